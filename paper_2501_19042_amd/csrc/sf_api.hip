@@ -3,6 +3,7 @@
 #include "swarmsf.h"
 #include "sf_internal.h"
 #include "sf_fast.h"
+#include "sf_f64.h"
 #include "sf_adjoint.h"
 #include "sf_eqqp.h"
 
@@ -251,15 +252,18 @@ struct Plan {
 
 struct sf_handle_s {
   int device = 0;
+  int ncu = 256;                 // compute units of that device
   void* scratch = nullptr;       // adjoint recompute states, grown on demand
   size_t scratch_bytes = 0;
   void* eq_part = nullptr;       // per-chunk partial sums of the equality layer's reverse mode
   size_t eq_part_bytes = 0;
   std::vector<HostCfg> cfgs;
+  void* d_tables = nullptr;      // the one device allocation that the tables below point into
   sf::DevCfg* d_cfgs = nullptr;
   double* d_tab64 = nullptr;
   float* d_tab32 = nullptr;
   void* d_a16 = nullptr;         // 16-bit S1 basis operands of the MFMA kernels
+  double* d_a64 = nullptr;       // basis operands of the FP64 matrix-core kernels
   hipStream_t cap_stream = nullptr;   // stream used to capture launch graphs
   std::vector<Plan*> plans;
   std::mutex mu;
@@ -763,6 +767,8 @@ sf_status sf_setup(const sf_config* cfgs, int32_t n_cfgs, sf_handle* out) {
     delete h;
     return hip_fail(e, "hipGetDevice");
   }
+  if (hipDeviceGetAttribute(&h->ncu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || h->ncu < 1)
+    h->ncu = 256;
   std::vector<double> all;
   std::vector<sf::DevCfg> devs;
   for (int i = 0; i < n_cfgs; ++i) {
@@ -806,14 +812,39 @@ sf_status sf_setup(const sf_config* cfgs, int32_t n_cfgs, sf_handle* out) {
     h->cfgs[i].dev.off_a32 = d.off_a32;
   }
   if (a16.empty()) a16.resize(8);
-  e = hipMalloc(&h->d_cfgs, devs.size() * sizeof(sf::DevCfg));
-  if (e == hipSuccess) e = hipMalloc(&h->d_tab64, all.size() * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&h->d_tab32, all32.size() * sizeof(float));
-  if (e == hipSuccess) e = hipMemcpy(h->d_cfgs, devs.data(), devs.size() * sizeof(sf::DevCfg), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(h->d_tab64, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(h->d_tab32, all32.data(), all32.size() * sizeof(float), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMalloc(&h->d_a16, a16.size() * sizeof(uint16_t));
-  if (e == hipSuccess) e = hipMemcpy(h->d_a16, a16.data(), a16.size() * sizeof(uint16_t), hipMemcpyHostToDevice);
+  std::vector<double> a64;
+  for (size_t i = 0; i < devs.size(); ++i) {
+    sf::DevCfg& d = devs[i];
+    d.off_a64 = -1;
+    if (sf::f64_cfg_covered(d)) {
+      d.off_a64 = (int64_t)a64.size();
+      a64.resize(a64.size() + sf::a64_entries(d));
+      sf::a64_fill(d, all.data() + d.off_basis, a64.data() + d.off_a64);
+    }
+    h->cfgs[i].dev.off_a64 = d.off_a64;
+  }
+  if (a64.empty()) a64.resize(4);
+  // one allocation and one copy for all tables
+  std::vector<unsigned char> host;
+  auto put = [&](const void* src, size_t bytes) {
+    const size_t off = (host.size() + 255) & ~(size_t)255;
+    host.resize(off + bytes);
+    std::memcpy(host.data() + off, src, bytes);
+    return off;
+  };
+  const size_t o_cfgs = put(devs.data(), devs.size() * sizeof(sf::DevCfg));
+  const size_t o_tab64 = put(all.data(), all.size() * sizeof(double));
+  const size_t o_tab32 = put(all32.data(), all32.size() * sizeof(float));
+  const size_t o_a16 = put(a16.data(), a16.size() * sizeof(uint16_t));
+  const size_t o_a64 = put(a64.data(), a64.size() * sizeof(double));
+  e = hipMalloc(&h->d_tables, host.size());
+  if (e == hipSuccess) e = hipMemcpy(h->d_tables, host.data(), host.size(), hipMemcpyHostToDevice);
+  unsigned char* base = static_cast<unsigned char*>(h->d_tables);
+  h->d_cfgs = reinterpret_cast<sf::DevCfg*>(base + o_cfgs);
+  h->d_tab64 = reinterpret_cast<double*>(base + o_tab64);
+  h->d_tab32 = reinterpret_cast<float*>(base + o_tab32);
+  h->d_a16 = base + o_a16;
+  h->d_a64 = reinterpret_cast<double*>(base + o_a64);
   if (e != hipSuccess) {
     sf_destroy(h);
     return hip_fail(e, "sf_setup upload");
@@ -831,10 +862,7 @@ sf_status sf_setup(const sf_config* cfgs, int32_t n_cfgs, sf_handle* out) {
 void sf_destroy(sf_handle h) {
   if (!h) return;
   for (Plan* p : h->plans) free_plan(p);
-  if (h->d_cfgs) (void)hipFree(h->d_cfgs);
-  if (h->d_tab64) (void)hipFree(h->d_tab64);
-  if (h->d_tab32) (void)hipFree(h->d_tab32);
-  if (h->d_a16) (void)hipFree(h->d_a16);
+  if (h->d_tables) (void)hipFree(h->d_tables);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   if (h->scratch) (void)hipFree(h->scratch);
   if (h->eq_part) (void)hipFree(h->eq_part);
@@ -895,7 +923,22 @@ sf_status sf_project(sf_handle h, const sf_batch* batch, int32_t precision, cons
   if (precision > SF_FP32 && !fp && (flags & (SF_RESID_HISTORY | SF_GENERIC_KERNEL)))
     return fail(SF_EUNSUPPORTED, "the MFMA precisions cannot be combined with SF_RESID_HISTORY or SF_GENERIC_KERNEL");
   // the generic kernel takes every work item without an MFMA plan, else the uncovered ones (if any)
-  const bool gen_part = !fp || p->n_items_gen > 0;
+  // (FP64: the matrix-core kernel where it covers the whole batch, all of one dimension)
+  int f64_W = 0, f64_R = 1, f64_D = 0;
+  size_t f64_lds = 0;
+  if (precision == SF_FP64 && !(flags & (SF_RESID_HISTORY | SF_GENERIC_KERNEL))) {
+    std::vector<const sf::DevCfg*> used;
+    bool covered = true;
+    for (int32_t s : p->slots_used) {
+      const sf::DevCfg& c = h->cfgs[s].dev;
+      covered = covered && c.off_a64 >= 0 && (f64_D == 0 || c.D == f64_D);
+      f64_D = c.D;
+      if (c.n > 16) f64_R = 2;
+      used.push_back(&c);
+    }
+    if (covered) f64_W = sf::f64_waves(used.data(), (int)used.size(), f64_R, p->n_items, h->ncu, &f64_lds);
+  }
+  const bool gen_part = f64_W == 0 && (!fp || p->n_items_gen > 0);
   if (gen_part) {
     st = pick_tile(h, p, elem, generic_bytes, &a.tile, &a.lds_bytes);
     if (st != SF_OK) return st;
@@ -919,6 +962,10 @@ sf_status sf_project(sf_handle h, const sf_batch* batch, int32_t precision, cons
     }
     if (precision == SF_FP64) {
       b.tab = h->d_tab64;
+      if (f64_W > 0) {
+        b.lds_bytes = f64_lds;
+        return sf::launch_f64_project(b, h->d_a64, f64_D, f64_R, f64_W);
+      }
       return sf::launch_generic_project<double>(b);
     }
     b.tab = h->d_tab32;

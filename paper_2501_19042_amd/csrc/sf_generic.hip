@@ -15,8 +15,8 @@
 // structure J (x) X0 + (I - J) (x) X1 with J = 11^T/n (the pair incidence gives
 // F_o^T F_o = (nI - 11^T) (x) P^T P), so the step costs O(n m_f^2) per axis.
 //
-// This path serves FP64 (parity with the oracle) and plain FP32 for any shape whose
-// LDS plan fits; the MFMA kernels cover the production shapes.
+// This path serves residual histories and any shape whose LDS plan fits, in FP64 and
+// FP32; the MFMA kernels (fp32, 16-bit forms and FP64) cover the production shapes.
 #include "sf_generic_impl.h"
 
 namespace sf {

@@ -39,6 +39,7 @@ struct DevCfg {
   int64_t off_basis, off_X1, off_X01, off_Bmap, off_Gfx, off_Rfx;
   int64_t off_a16[2];     // 16-byte offsets of the bf16 / fp16 S1 operand tables (MFMA path)
   int64_t off_a32;        // 16-byte offset of the fp32 S1 operand table (MFMA path)
+  int64_t off_a64;        // offset of the fp64 operand table (FP64 matrix-core path), -1: not covered
 };
 
 struct DevProblem {
