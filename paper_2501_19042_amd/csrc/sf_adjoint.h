@@ -36,10 +36,10 @@ hipError_t launch_adjoint(const AdjointArgs& a);
 
 size_t adjoint_lds_bytes(const DevCfg& c, int tile, size_t elem);
 
-// MFMA adjoint path (fp32; 3D, up to 16 robots, degree <= 15, horizon <= 256, no workspace rows).
-// The forward states of a checkpoint segment are recomputed by the forward MFMA kernel into
-// `states` ([len + 1][2][stride], stride = the batch's coefficient count); the cotangents of (xi,
-// lambda, xi_bar) are carried between segments in `carry` ([3][stride]).
+// MFMA adjoint path (fp32; 3D, up to 32 robots, degree <= 15, horizon <= 256).  The forward states of one or
+// more checkpoint segments are recomputed by the forward MFMA kernel into `states` ([segment - seg0][every +
+// 1][2][stride], stride = the batch's coefficient count); the cotangents of (xi, lambda, xi_bar) are carried
+// between launches in `carry` ([3][stride]).
 struct AdjFastArgs {
   const DevCfg* cfgs;
   const float* tab;
@@ -49,31 +49,28 @@ struct AdjFastArgs {
   int32_t n_items;
   const float* states;
   int64_t stride;
-  int32_t s0, len, iters;        // the segment's first iteration and length, total iterations
+  int32_t every, seg0;           // checkpoint interval, first segment in `states`
+  int32_t k_begin, k_end, iters; // the launch walks iterations k_end - 1 .. k_begin of iters
   const float* w_fpr;
-  const float* g_xi_out;         // first segment without the final-residual term: carries start here
+  const float* g_resid;          // final-residual term only
+  const float* g_xi_out;         // without the final-residual term the first launch starts from these
   const float* g_lam_out;
   bool init;                     // initialise the carries from g_xi_out / g_lam_out (else read them)
   float* carry;
   const float* pend;             // cotangent of xi^{K-1} from the final-residual term, or NULL
-  float* g_xi0;                  // last segment (s0 = 0): outputs instead of carries (any may be NULL)
+  float* pend_out;               // ... and where that term writes it
+  float* g_xi0;                  // last launch (k_begin = 0): outputs instead of carries (any may be NULL)
   float* g_lam0;
   float* g_xi_bar;
   bool last;
-  size_t lds_bytes;
   hipStream_t stream;
 };
 
-// Whether a config is covered by the MFMA adjoint path, its LDS bytes, and the reverse sweep over
-// one segment.
+// Whether a config is covered by the MFMA adjoint path; the reverse sweep over the segments in `states`; the
+// final-residual term (from the last two states, into the carries and pend_out).  R, KS: robot tiles of 16
+// and coefficient steps of 4 of the whole batch, cfgs the configs it uses.
 bool adjoint_fast_supported(const DevCfg& c);
-size_t adjoint_fast_lds_bytes(const DevCfg& c);
-hipError_t launch_adjoint_fast(const AdjFastArgs& a, int KS);
-// The final-residual term for that path (see sf_adjoint.hip): one workgroup per (sample, time tile
-// of a.tile steps) with per-tile partials in `part` ([n_tiles][2][stride]) and an in-order
-// reduction into the carries (gxi, glam, gxb) and pend.
-size_t adjoint_resid_tile_lds_bytes(const DevCfg& c, int tile);
-hipError_t launch_adjoint_resid_tiles(const AdjointArgs& a, const float* states, int64_t stride, int slot,
-                                      float* part, int n_tiles, float* carry, float* pend);
+hipError_t launch_adjoint_fast(const AdjFastArgs& a, const DevCfg* const* cfgs, int n_cfgs, int R, int KS, int ncu);
+hipError_t launch_adjoint_resid(const AdjFastArgs& a, const DevCfg* const* cfgs, int n_cfgs, int R, int KS);
 
 }  // namespace sf

@@ -619,27 +619,27 @@ sf_status get_eq_chunks(sf_handle h, Plan* p) {
   return SF_OK;
 }
 
-// Reverse mode on the matrix cores (fp32; batches the MFMA forward kernels cover, up to 16 robots,
-// no workspace rows).  Per checkpoint segment, last first: the forward MFMA kernel recomputes the
-// segment's states from its checkpoint (with checkpoints every iteration into the scratch), the
-// final-residual term is formed once from the last two states, and the reverse sweep carries the
-// cotangents of (xi, lambda, xi_bar) to the segment's start.
+// Bytes of recomputed states that one group of checkpoint segments may take in the scratch (one segment may
+// take more): ten segments of ten iterations of 16 robots x 512 samples are 238 MB.
+constexpr size_t kSegmentStates = (size_t)256 << 20;
+
+// Reverse mode on the matrix cores (fp32; batches the MFMA forward kernels cover).  The checkpoint segments
+// are taken in groups, last first: the forward MFMA kernel recomputes the states of a group's segments from
+// their checkpoints (a single-shape batch: all of them in one launch), the final-residual term is formed once
+// from the last two states, and the reverse sweep carries the cotangents of (xi, lambda, xi_bar) to the
+// group's start.
 sf_status adjoint_fast_path(sf_handle h, Plan* p, int32_t precision, const void* xi_bar, const void* bvals,
                             int32_t iters, const float* ckpt, int32_t ckpt_every, const void* g_xi_out,
                             const void* g_lam_out, const void* g_resid, const void* w_fpr, void* g_xi0, void* g_lam0,
                             void* g_xi_bar, void* stream) {
   const int64_t stride = p->total_coef;
-  // final-residual term: one workgroup per (sample, time tile of kResidTile steps), per-tile partials
-  constexpr int kResidTile = 16;
-  int max_h = 1;
-  size_t rlds = 0;
-  for (int32_t sl : p->slots_used) {
-    max_h = std::max(max_h, h->cfgs[sl].dev.H);
-    rlds = std::max(rlds, sf::adjoint_resid_tile_lds_bytes(h->cfgs[sl].dev, kResidTile));
-  }
-  const int n_rtiles = g_resid ? (max_h + kResidTile - 1) / kResidTile : 0;
-  // states, carries, pend, and the residual term's per-tile partials
-  const size_t need = ((size_t)2 * (ckpt_every + 1) + 4 + 2 * (size_t)n_rtiles) * stride * sizeof(float);
+  const int nseg = (iters + ckpt_every - 1) / ckpt_every;
+  const int64_t seg_states = (int64_t)2 * (std::min(ckpt_every, iters) + 1) * stride;   // elements per segment
+  const int64_t fit = std::max<int64_t>(1, (int64_t)(kSegmentStates / sizeof(float)) / seg_states);
+  const int group = p->fast.batched ? 1 : (int)std::min<int64_t>(std::min<int64_t>(nseg, fit), INT32_MAX / p->n_items);
+  const int every = std::min(ckpt_every, iters);   // slots per segment in the scratch
+  // states, carries and pend
+  const size_t need = ((size_t)group * seg_states + (size_t)4 * stride) * sizeof(float);
   if (need > h->scratch_bytes) {
     if (h->scratch) (void)hipFree(h->scratch);
     h->scratch = nullptr;
@@ -647,16 +647,20 @@ sf_status adjoint_fast_path(sf_handle h, Plan* p, int32_t precision, const void*
     if (hipMalloc(&h->scratch, need) != hipSuccess) return fail(SF_ENOMEM, "adjoint scratch allocation failed");
     h->scratch_bytes = need;
   }
-  float* states = static_cast<float*>(h->scratch);
-  float* carry = states + (size_t)2 * (ckpt_every + 1) * stride;
+  float* carry = static_cast<float*>(h->scratch);
   float* pend = carry + 3 * stride;
-  float* rpart = pend + stride;
+  float* states = pend + stride;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  size_t lds = 0;
-  for (int32_t sl : p->slots_used) lds = std::max(lds, sf::adjoint_fast_lds_bytes(h->cfgs[sl].dev));
-  const int nseg = (iters + ckpt_every - 1) / ckpt_every;
-  for (int seg = nseg - 1; seg >= 0; --seg) {
-    const int s0 = seg * ckpt_every, len = std::min(ckpt_every, iters - s0);
+  int R = 1;
+  std::vector<const sf::DevCfg*> cfgs;
+  for (int32_t sl : p->slots_used) {
+    cfgs.push_back(&h->cfgs[sl].dev);
+    if (cfgs.back()->n > 16) R = 2;
+  }
+  // with more than 16 robots or a workspace the states are recomputed in fp32 whatever the forward's form
+  const int32_t rp = (p->fast.ws || R == 2) ? SF_FP32 : precision;
+  for (int hi = nseg; hi > 0;) {
+    const int lo = std::max(0, hi - group);
     sf::LaunchArgs la{};
     la.cfgs = h->d_cfgs;
     la.probs = p->d_probs;
@@ -664,40 +668,27 @@ sf_status adjoint_fast_path(sf_handle h, Plan* p, int32_t precision, const void*
     la.n_items = p->n_items;
     la.xi_bar = xi_bar;
     la.bvals = bvals;
-    la.xi0 = ckpt + (size_t)seg * 2 * stride;
-    la.lam0 = ckpt + (size_t)seg * 2 * stride + stride;
-    la.iters = len;
-    la.xi_out = states + (size_t)len * 2 * stride;
-    la.lam_out = states + (size_t)len * 2 * stride + stride;
+    la.xi0 = ckpt + (size_t)lo * 2 * stride;
+    la.lam0 = ckpt + (size_t)lo * 2 * stride + stride;
     la.ckpt = states;
     la.ckpt_every = 1;
     la.ckpt_stride = stride;
     la.stream = s;
-    hipError_t e = sf::fast_launch(p->fast, la, h->d_tab32, h->d_a16, precision);
-    if (e != hipSuccess) return hip_fail(e, "sf_project_backward recompute");
-    bool init = false;
-    const float* pendp = nullptr;
-    if (seg == nseg - 1) {
-      if (g_resid) {
-        sf::AdjointArgs ra{};
-        ra.cfgs = h->d_cfgs;
-        ra.tab = h->d_tab32;
-        ra.probs = p->d_probs;
-        ra.items = p->d_items;
-        ra.n_items = p->n_items;
-        ra.g_xi_out = g_xi_out;
-        ra.g_lam_out = g_lam_out;
-        ra.g_resid = g_resid;
-        ra.stream = s;
-        ra.tile = kResidTile;
-        ra.lds_bytes = rlds;
-        e = sf::launch_adjoint_resid_tiles(ra, states, stride, len - 1, rpart, n_rtiles, carry, pend);
-        if (e != hipSuccess) return hip_fail(e, "sf_project_backward final-residual term");
-        pendp = pend;
-      } else {
-        init = true;
-      }
+    hipError_t e;
+    if (p->fast.batched) {
+      la.iters = std::min(ckpt_every, iters - lo * ckpt_every);
+      la.xi_out = states + (size_t)la.iters * 2 * stride;
+      la.lam_out = states + (size_t)la.iters * 2 * stride + stride;
+      e = sf::fast_launch(p->fast, la, h->d_tab32, h->d_a16, rp);
+    } else {
+      la.iters = every;
+      la.nseg = hi - lo;
+      la.seg_in = 2 * stride;
+      la.seg_out = seg_states;
+      la.iters_total = iters - lo * ckpt_every;
+      e = sf::fast_launch_segments(p->fast, la, h->d_tab32, h->d_a16, rp);
     }
+    if (e != hipSuccess) return hip_fail(e, "sf_project_backward recompute");
     sf::AdjFastArgs f{};
     f.cfgs = h->d_cfgs;
     f.tab = h->d_tab32;
@@ -707,23 +698,31 @@ sf_status adjoint_fast_path(sf_handle h, Plan* p, int32_t precision, const void*
     f.n_items = p->n_items;
     f.states = states;
     f.stride = stride;
-    f.s0 = s0;
-    f.len = len;
+    f.every = every;
+    f.seg0 = lo;
+    f.k_begin = lo * ckpt_every;
+    f.k_end = std::min(iters, hi * ckpt_every);
     f.iters = iters;
     f.w_fpr = static_cast<const float*>(w_fpr);
+    f.g_resid = static_cast<const float*>(g_resid);
     f.g_xi_out = static_cast<const float*>(g_xi_out);
     f.g_lam_out = static_cast<const float*>(g_lam_out);
-    f.init = init;
     f.carry = carry;
-    f.pend = pendp;
-    f.last = seg == 0;
+    f.pend_out = pend;
+    f.stream = s;
+    if (hi == nseg && g_resid) {
+      e = sf::launch_adjoint_resid(f, cfgs.data(), (int)cfgs.size(), R, p->fast.KS);
+      if (e != hipSuccess) return hip_fail(e, "sf_project_backward final-residual term");
+    }
+    f.init = hi == nseg && !g_resid;
+    f.pend = g_resid ? pend : nullptr;
+    f.last = lo == 0;
     f.g_xi0 = static_cast<float*>(g_xi0);
     f.g_lam0 = static_cast<float*>(g_lam0);
     f.g_xi_bar = static_cast<float*>(g_xi_bar);
-    f.lds_bytes = lds;
-    f.stream = s;
-    e = sf::launch_adjoint_fast(f, p->fast.KS);
+    e = sf::launch_adjoint_fast(f, cfgs.data(), (int)cfgs.size(), R, p->fast.KS, h->ncu);
     if (e != hipSuccess) return hip_fail(e, "sf_project_backward reverse sweep");
+    hi = lo;
   }
   return SF_OK;
 }
@@ -1048,7 +1047,7 @@ sf_status sf_project_backward(sf_handle h, const sf_batch* batch, int32_t precis
   st = get_plan(h, batch, &p);
   if (st != SF_OK) return st;
   int64_t max_ndm = 0;
-  bool fast = precision != SF_FP64 && iters > 0 && p->fast.ok && p->n_items_gen == 0 && !(p->fast.ws);
+  bool fast = precision != SF_FP64 && iters > 0 && p->fast.ok && p->n_items_gen == 0;
   for (int32_t s : p->slots_used) {
     const sf::DevCfg& c = h->cfgs[s].dev;
     max_ndm = std::max<int64_t>(max_ndm, (int64_t)c.n * c.D * c.m);

@@ -54,6 +54,11 @@ hipError_t fast_launch_batched(const FastPlan& p, const LaunchArgs& a, const flo
 hipError_t fast_launch_single(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,
                               int precision, int W);
 
+// Recomputation of a.nseg checkpoint segments of a single-shape batch in one launch (LaunchArgs: nseg, seg_in,
+// seg_out, iters_total).
+hipError_t fast_launch_segments(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,
+                                int precision);
+
 // Number of 16-byte entries of the 16-bit S1 basis-operand table of one config (per precision).
 int64_t a16_entries(const DevCfg& c);
 // Fill the table for one config: [tile][basis][instruction][lane] of 8 x 16-bit values.

@@ -29,6 +29,13 @@ hipError_t fast_launch_single_p2_w1(const FastPlan&, const LaunchArgs&, const fl
 hipError_t fast_launch_batched_p2_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
                                      int);
 
+hipError_t fast_launch_segments_p0_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+hipError_t fast_launch_segments_p0_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+hipError_t fast_launch_segments_p1_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+hipError_t fast_launch_segments_p1_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+hipError_t fast_launch_segments_p2_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+hipError_t fast_launch_segments_p2_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+
 using fastk::fast_lds_plan;
 using fastk::waves_per_simd;
 
@@ -276,6 +283,19 @@ hipError_t fast_launch(const FastPlan& p, const LaunchArgs& a, const float* tab3
     return fast_launch_batched(p, a, tab32, a16, precision, p.tuned_gc[pi], W, 3);
   }
   return fast_launch_single(p, a, tab32, a16, precision, waves(p.tuned_w[pi]));
+}
+
+hipError_t fast_launch_segments(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,
+                                int precision) {
+  const uint4* t = static_cast<const uint4*>(a16);
+  switch (precision) {
+    case SF_FP32: return p.ws ? fast_launch_segments_p0_w1(p, a, tab32, t) : fast_launch_segments_p0_w0(p, a, tab32, t);
+    case SF_BF16: return p.ws ? fast_launch_segments_p1_w1(p, a, tab32, t) : fast_launch_segments_p1_w0(p, a, tab32, t);
+    case SF_FP16: return p.ws ? fast_launch_segments_p2_w1(p, a, tab32, t) : fast_launch_segments_p2_w0(p, a, tab32, t);
+    default:
+      g_fast_err = "precision not implemented in the MFMA kernels";
+      return hipErrorNotSupported;
+  }
 }
 
 hipError_t fast_launch_single(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,

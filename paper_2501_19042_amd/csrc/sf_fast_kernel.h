@@ -1443,6 +1443,28 @@ fast_project_kernel(FastArgs A) {
   for (int it = blockIdx.x; it < A.n_items; it += gridDim.x) fast_item<R, KS, W, MP, WS>(A, it, smem);
 }
 
+// Recomputes several checkpoint segments at once for the reverse mode: workgroup (segment, work item) runs
+// the segment's iterations from its checkpoint (xi0, lam0: that of the first segment, seg_in elements apart)
+// and writes the state of every iteration (ckpt: those of the first segment, seg_out apart), the last one
+// after them.  A segment has few iterations, so one launch per segment leaves the chip waiting for each
+// sample's set-up: 16 robots x 512 samples, ten segments of ten iterations, 70 us each, 440 us together.
+template <int R, int KS, int W, int MP, int WPE, int WS>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+fast_segments_kernel(FastArgs A, int nseg, int64_t seg_in, int64_t seg_out, int iters_total) {
+  extern __shared__ __align__(16) float smem[];
+  for (int it = blockIdx.x; it < A.n_items * nseg; it += gridDim.x) {
+    const int seg = it / A.n_items;
+    FastArgs B = A;
+    B.iters = min(A.iters, iters_total - seg * A.iters);
+    B.xi0 += seg * seg_in;
+    B.lam0 += seg * seg_in;
+    B.ckpt += seg * seg_out;
+    B.xi_out = B.ckpt + B.iters * 2 * A.ckpt_stride;
+    B.lam_out = B.xi_out + A.ckpt_stride;
+    fast_item<R, KS, W, MP, WS>(B, it - seg * A.n_items, smem);
+  }
+}
+
 // Persistent kernel over the work items of one robot-tile class (R tiles of 16 robots) of a
 // ragged batch: workgroups pull items (sorted by decreasing cost on the host) from an atomic
 // queue until it is empty.  Every wave reaches the exit once the queue is drained.
@@ -1497,6 +1519,33 @@ hipError_t launch_instance(const FastPlan& p, const LaunchArgs& a, const float* 
   return hipGetLastError();
 }
 
+
+template <int R, int KS, int W, int MP, int WS>
+hipError_t launch_segments_instance(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
+  auto kern = fast_segments_kernel<R, KS, W, MP, waves_per_simd(R, MP, W), WS>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes[W - 2][MP]);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.n_items * a.nseg)), dim3(64 * W), p.lds_bytes[W - 2][MP], a.stream,
+                     make_fast_args(a, tab32, a16), a.nseg, a.seg_in, a.seg_out, a.iters_total);
+  return hipGetLastError();
+}
+
+// Single-shape batch, at the waves per sample a small batch runs with (4, with a workspace 3).
+template <int MP, int WS>
+hipError_t launch_segments_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
+  constexpr int W = WS ? 3 : 4;
+  switch (p.R * 10 + p.KS) {
+    case 12: return launch_segments_instance<1, 2, W, MP, WS>(p, a, tab32, a16);
+    case 13: return launch_segments_instance<1, 3, W, MP, WS>(p, a, tab32, a16);
+    case 14: return launch_segments_instance<1, 4, W, MP, WS>(p, a, tab32, a16);
+    case 23: return launch_segments_instance<2, 3, W, MP, WS>(p, a, tab32, a16);
+    case 24: return launch_segments_instance<2, 4, W, MP, WS>(p, a, tab32, a16);
+    default: break;
+  }
+  fast_set_error("no kernel instance for this shape");
+  return hipErrorNotSupported;
+}
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_class(const FastClass& C, const FastArgs& f, int grid, int* queue, hipStream_t stream) {

@@ -13,4 +13,8 @@ hipError_t fast_launch_batched_p1_w1(const FastPlan& p, const LaunchArgs& a, con
   return fastk::launch_batched_mp<1, 1>(p, a, tab32, a16, grid, W, cls_mask);
 }
 
+hipError_t fast_launch_segments_p1_w1(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
+  return fastk::launch_segments_mp<1, 1>(p, a, tab32, a16);
+}
+
 }  // namespace sf

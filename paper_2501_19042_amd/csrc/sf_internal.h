@@ -72,6 +72,9 @@ struct LaunchArgs {
   void* ckpt;
   int32_t ckpt_every;
   int64_t ckpt_stride;           // total coefficient elements of the batch
+  int32_t nseg;                  // segments launch of the MFMA kernels: segments, elements between their
+  int64_t seg_in, seg_out;       // checkpoints and between their states, iterations from the first segment
+  int32_t iters_total;           // on (iters: those of a whole segment)
   int32_t tile;                  // time-tile length
   size_t lds_bytes;
   hipStream_t stream;
