@@ -587,16 +587,23 @@ sf_status autotune(sf_handle h, const Plan* p, sf::FastPlan& fp, const sf::Launc
   return SF_OK;
 }
 
-// Sample chunks of the equality-only QP layer: each problem's samples in runs of about 32K
-// coefficients (one workgroup each), and the first chunk of every problem.
+// Sample chunks of the equality-only QP layer (one workgroup each, see eq_chunk_samples) and the first
+// chunk of every problem.
 sf_status get_eq_chunks(sf_handle h, Plan* p) {
   if (p->d_eq_chunks) return SF_OK;
   std::vector<sf::WorkItem> ch;
   std::vector<int32_t> first;
+  int64_t base = 0;
+  for (const sf::DevProblem& pr : p->probs) {
+    const sf::DevCfg& c = h->cfgs[pr.cfg].dev;
+    const int per = sf::eq_chunk_samples(pr.count, c.n * c.D * c.m, 0);
+    base += (pr.count + per - 1) / per;
+  }
+  const int want = sf::eq_chunk_want(base, (int)p->probs.size());
   for (size_t q = 0; q < p->probs.size(); ++q) {
     const sf::DevProblem& pr = p->probs[q];
     const sf::DevCfg& c = h->cfgs[pr.cfg].dev;
-    const int per = std::max(1, 32768 / (c.n * c.D * c.m));
+    const int per = sf::eq_chunk_samples(pr.count, c.n * c.D * c.m, want);
     first.push_back((int32_t)ch.size());
     for (int s = 0; s < pr.count; s += per) ch.push_back(sf::WorkItem{(int32_t)q, s, std::min(per, pr.count - s), 0});
   }
@@ -1144,7 +1151,6 @@ sf_status sf_qp_equality(sf_handle h, const sf_batch* batch, int32_t precision, 
   a.in = xi_in;
   a.bvals = bvals;
   a.out = xi_out;
-  for (int32_t s : p->slots_used) a.lds_bytes = std::max(a.lds_bytes, sf::qp_equality_lds_bytes(h->cfgs[s].dev, elem));
   a.stream = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (precision == SF_FP64) {
@@ -1201,7 +1207,6 @@ sf_status sf_qp_equality_backward(sf_handle h, const sf_batch* batch, int32_t pr
   a.part_stride = stride;
   a.max_rows = stride / sf::kNFix;
   a.g_bvals = g_bvals;
-  for (int32_t s : p->slots_used) a.lds_bytes = std::max(a.lds_bytes, sf::qp_equality_lds_bytes(h->cfgs[s].dev, elem));
   a.stream = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (precision == SF_FP64) {
@@ -1234,24 +1239,28 @@ sf_status sf_qp_equality_backward_noalloc(sf_handle h, const sf_batch* batch, in
   std::lock_guard<std::mutex> lock(h->mu);
   sf_status st = check_device(h);
   if (st != SF_OK) return st;
-  // the batch's sizes, chunk count and the most LDS any of its problems needs, without a plan
-  // (building one allocates device memory)
+  // the batch's sizes and chunk count, without a plan (building one allocates device memory)
   sf::EqNoAllocBatch b{};
   b.n_probs = batch->n_problems;
-  int64_t n_chunks = 0;
+  int64_t base_chunks = 0;
   int32_t stride = 0;
-  size_t lds = 0;
   for (int p = 0; p < batch->n_problems; ++p) {
     const int32_t slot = batch->cfg_slot[p], cnt = batch->sample_count[p];
     if (slot < 0 || slot >= (int)h->cfgs.size()) return fail(SF_EINVAL, "cfg_slot out of range");
     if (cnt < 1) return fail(SF_EINVAL, "sample_count must be >= 1");
     const sf::DevCfg& c = h->cfgs[slot].dev;
-    const int per = std::max(1, 32768 / (c.n * c.D * c.m));
-    n_chunks += (cnt + per - 1) / per;
+    const int per = sf::eq_chunk_samples(cnt, c.n * c.D * c.m, 0);
+    base_chunks += (cnt + per - 1) / per;
     stride = std::max(stride, c.n * c.D * sf::kNFix);
-    lds = std::max(lds, sf::qp_equality_lds_bytes(c, elem));
     b.slot[p] = slot;
     b.count[p] = cnt;
+  }
+  b.want = sf::eq_chunk_want(base_chunks, b.n_probs);
+  int64_t n_chunks = 0;
+  for (int p = 0; p < b.n_probs; ++p) {
+    const sf::DevCfg& c = h->cfgs[b.slot[p]].dev;
+    const int per = sf::eq_chunk_samples(b.count[p], c.n * c.D * c.m, b.want);
+    n_chunks += (b.count[p] + per - 1) / per;
   }
   const sf::EqNoAllocLayout lay =
       sf::eq_noalloc_layout(b.n_probs, (int32_t)std::min<int64_t>(n_chunks, INT32_MAX), stride, elem);
@@ -1277,7 +1286,6 @@ sf_status sf_qp_equality_backward_noalloc(sf_handle h, const sf_batch* batch, in
   a.part_stride = stride;
   a.max_rows = stride / sf::kNFix;
   a.g_bvals = g_bvals;
-  a.lds_bytes = lds;
   a.stream = s;
   if (precision == SF_FP64) {
     a.tab = h->d_tab64;

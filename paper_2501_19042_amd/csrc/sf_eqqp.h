@@ -21,18 +21,30 @@ struct EqArgs {
   int32_t part_stride;            // slots per chunk (largest n D 6 of the batch)
   int32_t max_rows;               // largest n D of the batch (grid of the final sum)
   void* g_bvals;                 // reverse: [total boundary values], or NULL
-  size_t lds_bytes;
   hipStream_t stream;
 };
 
-size_t qp_equality_lds_bytes(const DevCfg& c, size_t elem);
-
+// Samples per chunk (one workgroup) of a problem of `count` samples of nDm coefficients: about 32K
+// coefficients, so that a workgroup's set-up is small beside its stream; in a batch of fewer than kEqSpread
+// such chunks the problem is cut into up to `want` chunks instead (eq_chunk_want; 0: not).  64 samples of 16
+// robots in two chunks left the chip to two workgroups: 11.8 us forward, 4.7 us in 64.
+constexpr int kEqSpread = 512;
+__host__ __device__ inline int eq_chunk_samples(int count, int nDm, int want) {
+  const int most = 32768 / nDm > 1 ? 32768 / nDm : 1;
+  if (want < 1) return most;
+  const int per = (count + want - 1) / want;
+  return per < most ? per : most;
+}
+inline int eq_chunk_want(int64_t base_chunks, int n_probs) {
+  return base_chunks < kEqSpread ? (kEqSpread / n_probs > 1 ? kEqSpread / n_probs : 1) : 0;
+}
 // Allocation-free reverse mode: a fixed device array of the library holds the problem and chunk
 // tables and the per-chunk partial sums.
 constexpr size_t kEqNoAllocBytes = (size_t)16 << 20;   // size of that array per GPU
 constexpr int kEqNoAllocMaxProblems = 64;               // problems per call
 struct EqNoAllocBatch {                                 // passed by value to the table kernel
   int32_t n_probs;
+  int32_t want;                                         // eq_chunk_want of the batch
   int32_t slot[kEqNoAllocMaxProblems];
   int32_t count[kEqNoAllocMaxProblems];
 };

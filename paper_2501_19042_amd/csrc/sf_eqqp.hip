@@ -5,9 +5,8 @@
 // Those rows touch only the three first and three last coefficients of each robot-axis (the
 // Bernstein end conditions), and restricted to them A is the invertible 6 x 6 block whose inverse
 // sf_setup stores as Bmap.  So the free coefficients pass through and the six pinned ones become
-// Bmap b.  The kernels stream the coefficients (HBM-bound); the pinned values of a problem are
-// formed once per workgroup in LDS, and an LDS table maps each position of a sample to its pinned
-// value or to "pass".
+// Bmap b.  The kernels stream the coefficients (HBM-bound), each thread owning fixed positions of the samples
+// of a chunk.
 #include "sf_eqqp.h"
 
 #include <algorithm>
@@ -16,26 +15,125 @@
 namespace sf {
 namespace {
 
-constexpr int kEqBlock = 256;
+constexpr int kEqBlock = 512;
 
-template <typename T> struct Vec16;
-template <> struct Vec16<float> { typedef float4 type; };
-template <> struct Vec16<double> { typedef double2 type; };
+// 16-byte accesses where the sample's size and the pointers allow, else single elements.
+template <typename T, int VW> struct Vec { typedef T type __attribute__((ext_vector_type(VW))); };
 
-// LDS per workgroup: pinned values [nD][6] (T) and the position table [nDm] (int).
-template <typename T>
-__device__ void eq_tables(const DevCfg& c, const T* __restrict__ Bmap, const T* __restrict__ bv, T* pin, int* tbl) {
-  const int nD = c.n * c.D, m = c.m, nDm = nD * m;
-  for (int q = threadIdx.x; q < nD * kNFix; q += kEqBlock) {
-    const int row = q / kNFix, r = q - row * kNFix;
-    T acc = T(0);
-    for (int s = 0; s < kNFix; ++s) acc = fma(Bmap[r * kNFix + s], bv[row * kNFix + s], acc);
-    pin[q] = acc;
+// The positions (groups of VW elements of a sample) of this thread and the samples it visits: a position is
+// a thread's for the whole chunk, so its role and pinned values (or sums) stay in registers.  With at most
+// kEqBlock positions the workgroup covers `step` samples at a time, else it walks the positions.
+template <typename F>
+__device__ __forceinline__ void for_positions(int nV, F body) {
+  if (nV <= kEqBlock) {
+    const int step = kEqBlock / nV, s0 = threadIdx.x / nV;
+    if (s0 < step) body(threadIdx.x - s0 * nV, s0, step);
+  } else {
+    for (int ev = threadIdx.x; ev < nV; ev += kEqBlock) body(ev, 0, 1);
   }
-  for (int e = threadIdx.x; e < nDm; e += kEqBlock) {
-    const int row = e / m, k = e - row * m;
-    const int r = k < 3 ? k : (k >= m - 3 ? k - (m - kNFix) : -1);
-    tbl[e] = r < 0 ? -1 : row * kNFix + r;
+}
+
+// Pinned slot of position e of a sample (row * 6 + r), -1: a free coefficient.
+__device__ __forceinline__ int eq_slot(int e, int m) {
+  const int row = e / m, k = e - row * m;
+  const int r = k < 3 ? k : (k >= m - 3 ? k - (m - kNFix) : -1);
+  return r < 0 ? -1 : row * kNFix + r;
+}
+
+// One chunk of the forward: free coefficients pass, pinned ones become Bmap b.  Four accesses in flight per
+// thread.  16 robots x 2^19 samples: 0.43 ms, 5.1 TB/s, the rate of a device copy.
+template <typename T, int VW>
+__device__ void eq_forward(int nDm, int m, int count, const T* __restrict__ Bmap, const T* __restrict__ bv, const T* xin,
+                           T* xout) {
+  typedef typename Vec<T, VW>::type V;
+  const int nV = nDm / VW;
+  for_positions(nV, [&](int ev, int s0, int step) {
+    T pin[VW];
+    bool fix[VW];
+#pragma unroll
+    for (int j = 0; j < VW; ++j) {
+      const int slot = eq_slot(ev * VW + j, m);
+      fix[j] = slot >= 0;
+      T acc = T(0);
+      if (fix[j]) {
+        const int row = slot / kNFix, r = slot - row * kNFix;
+        for (int s = 0; s < kNFix; ++s) acc = fma(Bmap[r * kNFix + s], bv[row * kNFix + s], acc);
+      }
+      pin[j] = acc;
+    }
+    const V* in = reinterpret_cast<const V*>(xin) + ev;
+    V* out = reinterpret_cast<V*>(xout) + ev;
+    auto put = [&](int s, V v) {
+#pragma unroll
+      for (int j = 0; j < VW; ++j) v[j] = fix[j] ? pin[j] : v[j];
+      out[(int64_t)s * nV] = v;
+    };
+    int s = s0;
+    for (; s + 3 * step < count; s += 4 * step) {
+      V v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = in[(int64_t)(s + u * step) * nV];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) put(s + u * step, v[u]);
+    }
+    for (; s < count; s += step) put(s, in[(int64_t)s * nV]);
+  });
+}
+
+// One chunk of the reverse mode in one pass: g_xi_in = g with the pinned positions zeroed (g_in may be NULL
+// or g itself), and per pinned slot the sum of g over the chunk's samples (part may be NULL), in a fixed
+// order: a thread's samples, then the `step` threads of a position in order (red: kEqBlock VW elements).
+// The sums and the zeroed copy in two kernels read g twice: 16 robots x 2^19 samples 0.65 ms, now 0.43 ms.
+template <typename T, int VW>
+__device__ void eq_reverse(int nDm, int m, int count, const T* g, T* g_in, T* __restrict__ part, T* red) {
+  typedef typename Vec<T, VW>::type V;
+  const int nV = nDm / VW;
+  for_positions(nV, [&](int ev, int s0, int step) {
+    bool fix[VW];
+    T sum[VW];
+#pragma unroll
+    for (int j = 0; j < VW; ++j) {
+      fix[j] = eq_slot(ev * VW + j, m) >= 0;
+      sum[j] = T(0);
+    }
+    const V* in = reinterpret_cast<const V*>(g) + ev;
+    V* out = reinterpret_cast<V*>(g_in) + ev;
+    auto put = [&](int s, V v) {
+#pragma unroll
+      for (int j = 0; j < VW; ++j) {
+        sum[j] += v[j];
+        v[j] = fix[j] ? T(0) : v[j];
+      }
+      if (g_in) out[(int64_t)s * nV] = v;
+    };
+    int s = s0;
+    for (; s + 3 * step < count; s += 4 * step) {
+      V v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = in[(int64_t)(s + u * step) * nV];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) put(s + u * step, v[u]);
+    }
+    for (; s < count; s += step) put(s, in[(int64_t)s * nV]);
+    if (part) {
+#pragma unroll
+      for (int j = 0; j < VW; ++j) {
+        if (step > 1) red[threadIdx.x * VW + j] = sum[j];
+        else if (fix[j]) part[eq_slot(ev * VW + j, m)] = sum[j];
+      }
+    }
+  });
+  if (part && nV <= kEqBlock && kEqBlock / nV > 1) {
+    __syncthreads();
+    const int step = kEqBlock / nV;
+    for (int e = threadIdx.x; e < nDm; e += kEqBlock) {
+      const int slot = eq_slot(e, m);
+      if (slot < 0) continue;
+      T acc = red[e];
+      for (int q = 1; q < step; ++q) acc += red[q * nDm + e];
+      part[slot] = acc;
+    }
+    __syncthreads();
   }
 }
 
@@ -45,180 +143,85 @@ __global__ void __launch_bounds__(kEqBlock)
 qp_equality_kernel(const DevCfg* __restrict__ cfgs, const T* __restrict__ tab, const DevProblem* __restrict__ probs,
                    const WorkItem* __restrict__ chunks, int n_chunks, const T* xin, const T* __restrict__ bvals,
                    T* xout) {
-  extern __shared__ __align__(16) unsigned char eq_raw[];
+  constexpr int VW = 16 / sizeof(T);
   for (int it = blockIdx.x; it < n_chunks; it += gridDim.x) {
     const WorkItem w = chunks[it];
     const DevProblem pr = probs[w.problem];
-    const DevCfg c = cfgs[pr.cfg];
-    const int nDm = c.n * c.D * c.m;
-    T* pin = reinterpret_cast<T*>(eq_raw);
-    int* tbl = reinterpret_cast<int*>(pin + c.n * c.D * kNFix);
-    eq_tables<T>(c, tab + c.off_Bmap, bvals + pr.bnd_off, pin, tbl);
-    __syncthreads();
-    const int64_t base = pr.coef_off + (int64_t)w.first * nDm;
-    const int64_t total = (int64_t)w.count * nDm;
-    constexpr int VW = 16 / sizeof(T);           // elements per 16-byte access
-    const bool vec = (nDm % VW) == 0 && ((uintptr_t)(xin + base) % 16) == 0 && ((uintptr_t)(xout + base) % 16) == 0;
-    if (vec) {
-      // 16-byte accesses: VW consecutive positions of one sample per access
-      typedef typename Vec16<T>::type V;
-      const int nV = nDm / VW, stepV = kEqBlock % nV;
-      int ev = threadIdx.x % nV;
-      const V* xv = reinterpret_cast<const V*>(xin + base);
-      V* ov = reinterpret_cast<V*>(xout + base);
-      const int64_t nvt = total / VW;
-      auto fix = [&](V& v, int at) {
-        T* pv = reinterpret_cast<T*>(&v);
-#pragma unroll
-        for (int j = 0; j < VW; ++j) {
-          const int p = tbl[at * VW + j];
-          pv[j] = p < 0 ? pv[j] : pin[p < 0 ? 0 : p];
-        }
-      };
-      int64_t idx = threadIdx.x;
-      // four accesses in flight per thread: loads first, then the fix-ups and stores
-      for (; idx + 3 * kEqBlock < nvt; idx += 4 * kEqBlock) {
-        V v[4];
-        int at[4];
-        at[0] = ev;
-#pragma unroll
-        for (int u = 1; u < 4; ++u) {
-          at[u] = at[u - 1] + stepV;
-          if (at[u] >= nV) at[u] -= nV;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = xv[idx + u * kEqBlock];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          fix(v[u], at[u]);
-          ov[idx + u * kEqBlock] = v[u];
-        }
-        ev = at[3] + stepV;
-        if (ev >= nV) ev -= nV;
-      }
-      for (; idx < nvt; idx += kEqBlock) {
-        V v = xv[idx];
-        fix(v, ev);
-        ov[idx] = v;
-        ev += stepV;
-        if (ev >= nV) ev -= nV;
-      }
-    } else {
-      // position within the sample, advanced without a division per element
-      const int step = kEqBlock % nDm;
-      int e = threadIdx.x % nDm;
-      for (int64_t idx = threadIdx.x; idx < total; idx += kEqBlock) {
-        const T v = xin[base + idx];
-        const int p = tbl[e];
-        xout[base + idx] = p < 0 ? v : pin[p];
-        e += step;
-        if (e >= nDm) e -= nDm;
-      }
-    }
-    __syncthreads();
+    const DevCfg& c = cfgs[pr.cfg];
+    const int m = c.m, nDm = c.n * c.D * m;
+    const T* in = xin + pr.coef_off + (int64_t)w.first * nDm;
+    T* out = xout + pr.coef_off + (int64_t)w.first * nDm;
+    const bool vec = nDm % VW == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)out % 16 == 0;
+    if (vec) eq_forward<T, VW>(nDm, m, w.count, tab + c.off_Bmap, bvals + pr.bnd_off, in, out);
+    else eq_forward<T, 1>(nDm, m, w.count, tab + c.off_Bmap, bvals + pr.bnd_off, in, out);
   }
 }
 
-// Reverse mode, part 1: g_xi_in = g with the pinned positions zeroed (streamed like the forward).
+// Reverse mode, part 1: the zeroed copy and the chunks' sums.  g_bvals is linear in these sums.
 template <typename T>
 __global__ void __launch_bounds__(kEqBlock)
 qp_equality_bwd_kernel(const DevCfg* __restrict__ cfgs, const DevProblem* __restrict__ probs,
-                       const WorkItem* __restrict__ chunks, int n_chunks, const T* g, T* g_in) {
-  extern __shared__ __align__(16) unsigned char eq_raw[];
+                       const WorkItem* __restrict__ chunks, int n_chunks, const T* g, T* g_in, T* __restrict__ part,
+                       int part_stride) {
+  constexpr int VW = 16 / sizeof(T);
+  __shared__ T red[kEqBlock * VW];
   for (int it = blockIdx.x; it < n_chunks; it += gridDim.x) {
     const WorkItem w = chunks[it];
     const DevProblem pr = probs[w.problem];
-    const DevCfg c = cfgs[pr.cfg];
+    const DevCfg& c = cfgs[pr.cfg];
     const int m = c.m, nDm = c.n * c.D * m;
-    int* keep = reinterpret_cast<int*>(eq_raw);
-    for (int e = threadIdx.x; e < nDm; e += kEqBlock) {
-      const int k = e % m;
-      keep[e] = (k < 3 || k >= m - 3) ? 0 : 1;
-    }
-    __syncthreads();
-    const int64_t base = pr.coef_off + (int64_t)w.first * nDm;
-    const int64_t total = (int64_t)w.count * nDm;
-    constexpr int VW = 16 / sizeof(T);
-    const bool vec = (nDm % VW) == 0 && ((uintptr_t)(g + base) % 16) == 0 && ((uintptr_t)(g_in + base) % 16) == 0;
-    if (vec) {
-      typedef typename Vec16<T>::type V;
-      const int nV = nDm / VW, stepV = kEqBlock % nV;
-      int ev = threadIdx.x % nV;
-      const V* gv = reinterpret_cast<const V*>(g + base);
-      V* ov = reinterpret_cast<V*>(g_in + base);
-      for (int64_t idx = threadIdx.x; idx < total / VW; idx += kEqBlock) {
-        V v = gv[idx];
-        T* pv = reinterpret_cast<T*>(&v);
-#pragma unroll
-        for (int j = 0; j < VW; ++j) pv[j] = keep[ev * VW + j] ? pv[j] : T(0);
-        ov[idx] = v;
-        ev += stepV;
-        if (ev >= nV) ev -= nV;
-      }
-    } else {
-      const int step = kEqBlock % nDm;
-      int e = threadIdx.x % nDm;
-      for (int64_t idx = threadIdx.x; idx < total; idx += kEqBlock) {
-        const T v = g[base + idx];
-        g_in[base + idx] = keep[e] ? v : T(0);
-        e += step;
-        if (e >= nDm) e -= nDm;
-      }
-    }
-    __syncthreads();
+    const T* in = g + pr.coef_off + (int64_t)w.first * nDm;
+    T* out = g_in ? g_in + pr.coef_off + (int64_t)w.first * nDm : nullptr;
+    T* sums = part ? part + (int64_t)it * part_stride : nullptr;
+    const bool vec = nDm % VW == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)out % 16 == 0;
+    if (vec) eq_reverse<T, VW>(nDm, m, w.count, in, out, sums, red);
+    else eq_reverse<T, 1>(nDm, m, w.count, in, out, sums, red);
   }
 }
 
-// Reverse mode, part 2: per chunk and pinned slot (row, r), the sum over the chunk's samples of
-// g at that slot (four accumulators, fixed order).  g_bvals is linear in these sums.
+// Reverse mode, part 2: one workgroup per (problem, robot-axis row) sums the row's six slots over the problem's
+// chunks and writes g_bvals[row][col] = sum_r Bmap[r][col] G[r].  A lane owns (chunk of ten, slot), so that a
+// row's slots, contiguous in a chunk's sums, are read together, once; fixed order.  Bound by the latency of
+// the strided reads: 8457 chunks of 16 robots took 70 us with a wave per slot, 27 us now.
+constexpr int kSumWaves = 16, kSumChunks = 10;   // per workgroup, per wave
 template <typename T>
-__global__ void __launch_bounds__(kEqBlock)
-qp_equality_part_kernel(const DevCfg* __restrict__ cfgs, const DevProblem* __restrict__ probs,
-                        const WorkItem* __restrict__ chunks, int n_chunks, const T* __restrict__ g,
-                        T* __restrict__ part, int part_stride) {
-  for (int it = blockIdx.x; it < n_chunks; it += gridDim.x) {
-    const WorkItem w = chunks[it];
-    const DevProblem pr = probs[w.problem];
-    const DevCfg c = cfgs[pr.cfg];
-    const int m = c.m, nDm = c.n * c.D * m;
-    const int64_t base = pr.coef_off + (int64_t)w.first * nDm;
-    for (int q = threadIdx.x; q < c.n * c.D * kNFix; q += kEqBlock) {
-      const int row = q / kNFix, r = q - row * kNFix;
-      const T* gp = g + base + row * m + (r < 3 ? r : m - kNFix + r);
-      T a0 = T(0), a1 = T(0), a2 = T(0), a3 = T(0);
-      int s = 0;
-      for (; s + 4 <= w.count; s += 4) {
-        a0 += gp[(int64_t)s * nDm];
-        a1 += gp[(int64_t)(s + 1) * nDm];
-        a2 += gp[(int64_t)(s + 2) * nDm];
-        a3 += gp[(int64_t)(s + 3) * nDm];
-      }
-      for (; s < w.count; ++s) a0 += gp[(int64_t)s * nDm];
-      part[(int64_t)it * part_stride + q] = (a0 + a1) + (a2 + a3);
-    }
-  }
-}
-
-// Reverse mode, part 3: one workgroup per (problem, robot-axis row); wave r sums slot (row, r)
-// over the problem's chunks (lanes strided, then a fixed butterfly), and g_bvals[row][col] =
-// sum_r Bmap[r][col] G[r].  Deterministic.
-template <typename T>
-__global__ void __launch_bounds__(64 * kNFix)
+__global__ void __launch_bounds__(64 * kSumWaves)
 qp_equality_bsum_kernel(const DevCfg* __restrict__ cfgs, const T* __restrict__ tab,
                         const DevProblem* __restrict__ probs, int n_probs, const int* __restrict__ chunk_first,
                         const T* __restrict__ part, int part_stride, T* __restrict__ g_bvals) {
+  __shared__ T red[kSumWaves][kSumChunks * kNFix];
   __shared__ T G[kNFix];
   const int row = blockIdx.x;
   for (int p = blockIdx.y; p < n_probs; p += gridDim.y) {
     const DevProblem pr = probs[p];
-    const DevCfg c = cfgs[pr.cfg];
+    const DevCfg& c = cfgs[pr.cfg];
     if (row >= c.n * c.D) continue;               // uniform over the workgroup
-    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
-    T acc = T(0);
-    for (int ch = chunk_first[p] + lane; ch < chunk_first[p + 1]; ch += 64)
-      acc += part[(int64_t)ch * part_stride + row * kNFix + r];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0) G[r] = acc;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < kSumChunks * kNFix) {
+      constexpr int kStep = kSumWaves * kSumChunks;
+      const T* src = part + row * kNFix + lane % kNFix;
+      const int end = chunk_first[p + 1];
+      T a[4] = {T(0), T(0), T(0), T(0)};
+      int ch = chunk_first[p] + wave * kSumChunks + lane / kNFix;
+      for (; ch + 3 * kStep < end; ch += 4 * kStep) {
+        T v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src[(int64_t)(ch + kStep * u) * part_stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] += v[u];
+      }
+      for (; ch < end; ch += kStep) a[0] += src[(int64_t)ch * part_stride];
+      red[wave][lane] = (a[0] + a[1]) + (a[2] + a[3]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      T v = T(0);
+      if (lane < kSumChunks * kNFix)
+        for (int ww = 0; ww < kSumWaves; ++ww) v += red[ww][lane];
+      T acc = v;
+      for (int q = 1; q < kSumChunks; ++q) acc += __shfl(v, lane + q * kNFix);
+      if (lane < kNFix) G[lane] = acc;
+    }
     __syncthreads();
     if (threadIdx.x < kNFix) {
       const T* Bmap = tab + c.off_Bmap;
@@ -232,7 +235,7 @@ qp_equality_bsum_kernel(const DevCfg* __restrict__ cfgs, const T* __restrict__ t
 
 // Allocation-free reverse mode: the tables of a batch, built on the device from its (config slot,
 // sample count) list, in the layout and order of the host-built plan (get_plan / get_eq_chunks):
-// problems packed in order, chunks of max(1, 32768 / (n D m)) samples.
+// problems packed in order, chunks of eq_chunk_samples samples.
 __global__ void __launch_bounds__(256)
 eq_noalloc_tables_kernel(const DevCfg* __restrict__ cfgs, EqNoAllocBatch b, DevProblem* __restrict__ probs,
                          WorkItem* __restrict__ chunks, int32_t* __restrict__ chunk_first) {
@@ -249,7 +252,7 @@ eq_noalloc_tables_kernel(const DevCfg* __restrict__ cfgs, EqNoAllocBatch b, DevP
       pr.bnd_off = bnd;
       pr.sample_base = smp;
       probs[p] = pr;
-      per[p] = max(1, 32768 / (c.n * c.D * c.m));
+      per[p] = eq_chunk_samples(b.count[p], c.n * c.D * c.m, b.want);
       first[p] = ch;
       chunk_first[p] = ch;
       ch += (b.count[p] + per[p] - 1) / per[p];
@@ -315,38 +318,26 @@ hipError_t launch_eq_noalloc_tables(const DevCfg* cfgs, const EqNoAllocBatch& b,
   return hipGetLastError();
 }
 
-size_t qp_equality_lds_bytes(const DevCfg& c, size_t elem) {
-  return (size_t)c.n * c.D * kNFix * elem + (size_t)c.n * c.D * c.m * sizeof(int);
-}
-
 template <typename T>
 hipError_t launch_qp_equality(const EqArgs& a) {
   if (a.n_chunks == 0) return hipSuccess;
   const int grid = a.n_chunks;
   if (a.forward) {
-    hipLaunchKernelGGL(qp_equality_kernel<T>, dim3(grid), dim3(kEqBlock), a.lds_bytes, a.stream, a.cfgs,
+    hipLaunchKernelGGL(qp_equality_kernel<T>, dim3(grid), dim3(kEqBlock), 0, a.stream, a.cfgs,
                        static_cast<const T*>(a.tab), a.probs, a.chunks, a.n_chunks, static_cast<const T*>(a.in),
                        static_cast<const T*>(a.bvals), static_cast<T*>(a.out));
     return hipGetLastError();
   }
-  // the sums read g before g_in overwrites it (they may be the same array)
-  if (a.g_bvals) {
-    hipLaunchKernelGGL(qp_equality_part_kernel<T>, dim3(grid), dim3(kEqBlock), 0, a.stream, a.cfgs, a.probs,
-                       a.chunks, a.n_chunks, static_cast<const T*>(a.in), static_cast<T*>(a.part), a.part_stride);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(qp_equality_bsum_kernel<T>, dim3(a.max_rows, std::min(a.n_probs, 65535)), dim3(64 * kNFix), 0,
-                       a.stream, a.cfgs, static_cast<const T*>(a.tab), a.probs, a.n_probs, a.chunk_first,
-                       static_cast<const T*>(a.part), a.part_stride, static_cast<T*>(a.g_bvals));
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (a.out) {
-    hipLaunchKernelGGL(qp_equality_bwd_kernel<T>, dim3(grid), dim3(kEqBlock), a.lds_bytes, a.stream, a.cfgs,
-                       a.probs, a.chunks, a.n_chunks, static_cast<const T*>(a.in), static_cast<T*>(a.out));
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  T* part = a.g_bvals ? static_cast<T*>(a.part) : nullptr;
+  hipLaunchKernelGGL(qp_equality_bwd_kernel<T>, dim3(grid), dim3(kEqBlock), 0, a.stream, a.cfgs, a.probs, a.chunks,
+                     a.n_chunks, static_cast<const T*>(a.in), static_cast<T*>(a.out), part, a.part_stride);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !part) return e;
+  hipLaunchKernelGGL(qp_equality_bsum_kernel<T>, dim3(a.max_rows, std::min(a.n_probs, 65535)),
+                     dim3(64 * kSumWaves), 0,
+                     a.stream, a.cfgs, static_cast<const T*>(a.tab), a.probs, a.n_probs, a.chunk_first, part,
+                     a.part_stride, static_cast<T*>(a.g_bvals));
+  return hipGetLastError();
 }
 
 template hipError_t launch_qp_equality<double>(const EqArgs&);
