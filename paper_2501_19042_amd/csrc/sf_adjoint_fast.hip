@@ -203,9 +203,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
     uint16_t* lists = reinterpret_cast<uint16_t*>(wbuf + Lp.list);
     {
       const int tid = threadIdx.x;
-      for (int i = tid; i < n; i += nthr) {
-        int p = i * n - i * (i + 1) / 2;
-        for (int j = i + 1; j < n; ++j) spairs[p++] = (uint16_t)(i | (j << 8));
+      for (int q = tid; q < n * n; q += nthr) {
+        const int i = q / n, j = q - i * n;
+        if (j > i) spairs[i * n - i * (i + 1) / 2 + j - i - 1] = (uint16_t)(i | (j << 8));
       }
       for (int q = tid; q < mf * mf; q += nthr) {
         sX1[q] = (A.tab + c.off_X1)[q];
@@ -632,9 +632,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     float* wbuf = smem + Lp.tiles + wave * Lp.per_wave;
     float *Xt = wbuf + Lp.xt, *Wt = wbuf + Lp.wt, *Ct = wbuf + Lp.ct, *bb = wbuf + Lp.bb;
     uint16_t* tl = reinterpret_cast<uint16_t*>(wbuf + Lp.list);
-    for (int i = tid; i < n; i += nthr) {
-      int p = i * n - i * (i + 1) / 2;
-      for (int j = i + 1; j < n; ++j) spairs[p++] = (uint16_t)(i | (j << 8));
+    for (int q = tid; q < n * n; q += nthr) {
+      const int i = q / n, j = q - i * n;
+      if (j > i) spairs[i * n - i * (i + 1) / 2 + j - i - 1] = (uint16_t)(i | (j << 8));
     }
     for (int q = tid; q < 3 * 4 * KS * NR; q += nthr) sxk[q] = sdl[q] = 0.0f;
     __syncthreads();

@@ -434,6 +434,21 @@ sf_status check_device(sf_handle h) {
   return SF_OK;
 }
 
+// Whether the FP64 matrix-core kernels cover every config of the batch, all of one dimension; the configs,
+// their dimension and robot tiles of 16.
+bool f64_covered(sf_handle h, const Plan* p, std::vector<const sf::DevCfg*>& used, int& D, int& R) {
+  D = 0;
+  R = 1;
+  for (int32_t s : p->slots_used) {
+    const sf::DevCfg& c = h->cfgs[s].dev;
+    if (c.off_a64 < 0 || (D != 0 && c.D != D)) return false;
+    D = c.D;
+    if (c.n > 16) R = 2;
+    used.push_back(&c);
+  }
+  return true;
+}
+
 // ------------------------------------------------------------------------------------
 // Autotuner of the persistent launch: times candidate grid sizes on the caller's batch and
 // buffers, keeps the fastest per (device, batch, shapes, precision) in a JSON-lines cache.
@@ -932,18 +947,9 @@ sf_status sf_project(sf_handle h, const sf_batch* batch, int32_t precision, cons
   // (FP64: the matrix-core kernel where it covers the whole batch, all of one dimension)
   int f64_W = 0, f64_R = 1, f64_D = 0;
   size_t f64_lds = 0;
-  if (precision == SF_FP64 && !(flags & (SF_RESID_HISTORY | SF_GENERIC_KERNEL))) {
-    std::vector<const sf::DevCfg*> used;
-    bool covered = true;
-    for (int32_t s : p->slots_used) {
-      const sf::DevCfg& c = h->cfgs[s].dev;
-      covered = covered && c.off_a64 >= 0 && (f64_D == 0 || c.D == f64_D);
-      f64_D = c.D;
-      if (c.n > 16) f64_R = 2;
-      used.push_back(&c);
-    }
-    if (covered) f64_W = sf::f64_waves(used.data(), (int)used.size(), f64_R, p->n_items, h->ncu, &f64_lds);
-  }
+  std::vector<const sf::DevCfg*> used;
+  if (precision == SF_FP64 && !(flags & (SF_RESID_HISTORY | SF_GENERIC_KERNEL)) && f64_covered(h, p, used, f64_D, f64_R))
+    f64_W = sf::f64_waves(used.data(), (int)used.size(), f64_R, p->n_items, h->ncu, &f64_lds);
   const bool gen_part = f64_W == 0 && (!fp || p->n_items_gen > 0);
   if (gen_part) {
     st = pick_tile(h, p, elem, generic_bytes, &a.tile, &a.lds_bytes);
@@ -1114,11 +1120,31 @@ sf_status sf_feasibility(sf_handle h, const sf_batch* batch, int32_t precision, 
   Plan* p = nullptr;
   st = get_plan(h, batch, &p);
   if (st != SF_OK) return st;
+  hipError_t e;
+  std::vector<const sf::DevCfg*> used;
+  int D = 0, R = 1;
+  if (f64_covered(h, p, used, D, R)) {
+    sf::CheckArgs a{};
+    a.cfgs = h->d_cfgs;
+    a.tab = h->d_tab64;
+    a.a64 = h->d_a64;
+    a.probs = p->d_probs;
+    a.items = p->d_items;
+    a.n_items = p->n_items;
+    a.xi = xi;
+    a.bvals = bvals;
+    a.viol = static_cast<double*>(viol_out);
+    for (const sf::DevCfg* c : used) a.lds_bytes = std::max(a.lds_bytes, sf::f64_check_lds_bytes(*c, R));
+    a.stream = static_cast<hipStream_t>(stream);
+    e = sf::launch_f64_check(a, precision == SF_FP64, D, R);
+    if (e != hipSuccess) return hip_fail(e, "sf_feasibility launch");
+    return SF_OK;
+  }
   int tile = 0;
   size_t lds = 0;
   st = pick_tile(h, p, sizeof(double), feas_bytes, &tile, &lds);
   if (st != SF_OK) return st;
-  hipError_t e = sf::launch_feasibility(h->d_cfgs, h->d_tab64, p->d_probs, p->d_items, p->n_items, xi,
+  e = sf::launch_feasibility(h->d_cfgs, h->d_tab64, p->d_probs, p->d_items, p->n_items, xi,
                                         precision == SF_FP64, bvals, static_cast<double*>(viol_out), tile, lds,
                                         static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "sf_feasibility launch");

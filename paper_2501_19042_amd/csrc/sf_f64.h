@@ -17,4 +17,21 @@ void a64_fill(const DevCfg& c, const double* P3, double* out);
 int f64_waves(const DevCfg* const* cfgs, int n_cfgs, int R, int64_t n_items, int ncu, size_t* lds);
 hipError_t launch_f64_project(const LaunchArgs& a, const double* a64, int D, int R, int W);
 
+// FP64 feasibility check of a batch of covered configs (violations as in launch_feasibility).
+struct CheckArgs {
+  const DevCfg* cfgs;
+  const double* tab;
+  const double* a64;
+  const DevProblem* probs;
+  const WorkItem* items;
+  int32_t n_items;
+  const void* xi;
+  const void* bvals;
+  double* viol;
+  size_t lds_bytes;
+  hipStream_t stream;
+};
+size_t f64_check_lds_bytes(const DevCfg& c, int R);
+hipError_t launch_f64_check(const CheckArgs& a, bool dbl, int D, int R);
+
 }  // namespace sf

@@ -183,9 +183,9 @@ f64_project_kernel(F64Args A) {
     double* wbuf = sm + L.tiles + wave * L.per_wave;
     double *Xt = wbuf + L.xt, *Ct = wbuf + L.ct, *bb = wbuf + L.bb;
     uint16_t* lists = reinterpret_cast<uint16_t*>(wbuf + L.list);
-    for (int i = tid; i < n; i += nthr) {
-      int p = i * n - i * (i + 1) / 2;
-      for (int j = i + 1; j < n; ++j) spairs[p++] = (uint16_t)(i | (j << 8));
+    for (int q = tid; q < n * n; q += nthr) {
+      const int i = q / n, j = q - i * n;
+      if (j > i) spairs[i * n - i * (i + 1) / 2 + j - i - 1] = (uint16_t)(i | (j << 8));
     }
     for (int q = tid; q < mf * mf; q += nthr) {
       sX1[q] = (A.tab + c.off_X1)[q];
@@ -759,6 +759,228 @@ f64_project_kernel(F64Args A) {
   }
 }
 
+// ---------------------------------------------------------------------------------
+// FP64 feasibility check at the grid times, four waves per sample, time tiles as above.  The largest speeds
+// and workspace offsets come from the product registers.  The smallest separation of a tile is first taken at
+// one of its times; then only pairs whose boxes are nearer than that are visited at all of them, so the
+// minimum is that over every pair and time.  Bound by the FP64 matrix rate (16 robots: 27 products a tile of
+// 64 cycles, 5 us at 1024 samples) and the LDS reads of the pairs: 26 us, against 97 us in the generic kernel,
+// which visits every pair at every time and reads the basis from global memory.
+// ---------------------------------------------------------------------------------
+
+constexpr int kCheckW = 4;
+
+struct CheckLds {
+  int x, red, pairs, tiles, per_wave, total;   // in doubles
+  int xt, bb, list;
+};
+
+__host__ __device__ inline CheckLds check_plan(const DevCfg& c, int R) {
+  const int NR = 16 * R, D = c.D, Np = c.n * (c.n - 1) / 2;
+  CheckLds p;
+  int o = 0;
+  p.x = o; o += D * 16 * NR;                // [axis][16 coefficients][16R robots], zero outside
+  p.red = o; o += 5 * kCheckW;
+  p.pairs = o; o += (Np + 3) / 4;
+  p.tiles = o;
+  p.xt = 0;
+  p.bb = D * NR * 16;
+  p.list = p.bb + 2 * D * NR;
+  p.per_wave = p.list + (Np + 3) / 4;
+  o += kCheckW * p.per_wave;
+  p.total = o;
+  return p;
+}
+
+template <typename Tin, int D, int R>
+__global__ void __launch_bounds__(64 * kCheckW)
+f64_check_kernel(const DevCfg* __restrict__ cfgs, const double* __restrict__ tab, const double* __restrict__ a64,
+                 const DevProblem* __restrict__ probs, const WorkItem* __restrict__ items, int n_items,
+                 const Tin* __restrict__ xi, const Tin* __restrict__ bvals, double* __restrict__ viol) {
+  extern __shared__ __align__(16) double sm[];
+  constexpr int NR = 16 * R, nthr = 64 * kCheckW;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, grp = lane >> 4;
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const WorkItem w = items[it];
+    const DevProblem pr = probs[w.problem];
+    const DevCfg& c = cfgs[pr.cfg];
+    const CheckLds L = check_plan(c, R);
+    const int n = c.n, m = c.m, H = c.H, nDm = n * D * m, Np = n * (n - 1) / 2, NT = (H + 15) / 16, ks = (m + 3) / 4;
+    const double ia2 = c.inv_a2, ib2 = c.inv_b2;
+    const double wc[3] = {c.ws_c[0], c.ws_c[1], c.ws_c[2]}, wi[3] = {c.ws_ia2, c.ws_ia2, c.ws_ib2};
+    const double* basis = tab + c.off_basis;
+    const d4* tabA = reinterpret_cast<const d4*>(a64 + c.off_a64);
+    const Tin* bv = bvals + pr.bnd_off;
+    double *x = sm + L.x, *red = sm + L.red, *wbuf = sm + L.tiles + wave * L.per_wave;
+    double *Xt = wbuf + L.xt, *bb = wbuf + L.bb;
+    uint16_t* spairs = reinterpret_cast<uint16_t*>(sm + L.pairs);
+    uint16_t* tl = reinterpret_cast<uint16_t*>(wbuf + L.list);
+    for (int q = tid; q < D * 16 * NR; q += nthr) x[q] = 0.0;
+    for (int q = tid; q < n * n; q += nthr) {
+      const int i = q / n, j = q - i * n;
+      if (j > i) spairs[i * n - i * (i + 1) / 2 + j - i - 1] = (uint16_t)(i | (j << 8));
+    }
+    __syncthreads();
+    for (int sl = w.first; sl < w.first + w.count; ++sl) {
+      const int64_t coef = pr.coef_off + (int64_t)sl * nDm;
+      const int64_t sidx = pr.sample_base + sl;
+      for (int q = tid; q < nDm; q += nthr) {
+        const int row = q / m, k = q - row * m, i = row / D, d = row - i * D;
+        x[(d * 16 + k) * NR + i] = (double)xi[coef + q];
+      }
+      __syncthreads();
+      double smin = DBL_MAX, vmx = 0.0, amx = 0.0, bmx = 0.0, wmx = 0.0;
+      for (int q = tid; q < n * D * kNFix; q += nthr) {
+        const int row = q / kNFix, r = q - row * kNFix, i = row / D, d = row - i * D;
+        const double* brow = basis + ((size_t)(r % 3) * H + (r < 3 ? 0 : H - 1)) * m;
+        double acc = 0.0;
+#pragma unroll 4
+        for (int k = 0; k < m; ++k) acc = fma(brow[k], x[(d * 16 + k) * NR + i], acc);
+        bmx = fmax(bmx, fabs(acc - (double)bv[q]));
+      }
+      auto prod = [&](const d4 a, d4 (&Y)[R][D]) {
+        const double* xp = x + grp * NR + col;
+#pragma unroll
+        for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+          for (int d = 0; d < D; ++d) Y[rr][d] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          if (s < ks) {
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+              for (int d = 0; d < D; ++d) Y[rr][d] = mfma64(a[s], xp[(d * 16 + 4 * s) * NR + 16 * rr], Y[rr][d]);
+          }
+      };
+#pragma unroll 1
+      for (int tau = wave; tau < NT; tau += kCheckW) {
+        d4 Y[R][D];
+        // (rows past the horizon repeat the last grid time: no other value enters)
+        prod(tabA[(tau * 3 * 2) * 64 + lane], Y);
+#pragma unroll
+        for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            double w2 = 0.0;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+              Xt[at(d * NR + 16 * rr + col, 4 * r + grp)] = Y[rr][d][r];
+              const double v = Y[rr][d][r] - wc[d];
+              w2 += v * v * wi[d];
+            }
+            if (16 * rr + col < n) wmx = fmax(wmx, w2);
+          }
+#pragma unroll 1
+        for (int b = 1; b < 3; ++b) {
+          prod(tabA[((tau * 3 + b) * 2) * 64 + lane], Y);
+          double mx = 0.0;
+#pragma unroll
+          for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              double v2 = 0.0;
+#pragma unroll
+              for (int d = 0; d < D; ++d) v2 += Y[rr][d][r] * Y[rr][d][r];
+              if (16 * rr + col < n) mx = fmax(mx, v2);
+            }
+          if (b == 1) vmx = fmax(vmx, mx);
+          else amx = fmax(amx, mx);
+        }
+        wave_sync();
+        for (int row = lane; row < D * NR; row += 64) {
+          double lo = Xt[at(row, 0)], hi = lo;
+#pragma unroll
+          for (int t = 1; t < 16; ++t) {
+            const double v = Xt[at(row, t)];
+            lo = fmin(lo, v);
+            hi = fmax(hi, v);
+          }
+          bb[2 * row] = lo;
+          bb[2 * row + 1] = hi;
+        }
+        auto sep = [&](int code, int t) {
+          const int i = code & 255, j = code >> 8;
+          double s = 0.0;
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            const double r = Xt[at(d * NR + i, t)] - Xt[at(d * NR + j, t)];
+            s += r * r * (d == 2 ? ib2 : ia2);
+          }
+          return s;
+        };
+        for (int p = lane; p < Np; p += 64) smin = fmin(smin, sep(spairs[p], 0));
+        double near = smin;
+        for (int off = 32; off > 0; off >>= 1) near = fmin(near, __shfl_xor(near, off));
+        wave_sync();
+        int count = 0;
+        for (int base = 0; base < Np; base += 64) {
+          const int p = base + lane;
+          const int code = spairs[min(p, Np - 1)], i = code & 255, j = code >> 8;
+          double g2 = 0.0;
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            const double* bi = bb + 2 * (d * NR + i);
+            const double* bj = bb + 2 * (d * NR + j);
+            const double gap = fmax(0.0, fmax(bj[0] - bi[1], bi[0] - bj[1]));
+            g2 += gap * gap * (d == 2 ? ib2 : ia2);
+          }
+          const bool act = p < Np && g2 * (1.0 - 1e-12) < near;   // (far above the rounding of a gap)
+          const uint64_t mask = __ballot(act);
+          if (act)
+            tl[count + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0))] = (uint16_t)code;
+          count += __popcll(mask);
+        }
+        wave_sync();
+        for (int slot = grp; slot < count; slot += 4) smin = fmin(smin, sep(tl[slot], col));
+        wave_sync();
+      }
+      for (int off = 32; off > 0; off >>= 1) {
+        smin = fmin(smin, __shfl_xor(smin, off));
+        vmx = fmax(vmx, __shfl_xor(vmx, off));
+        amx = fmax(amx, __shfl_xor(amx, off));
+        bmx = fmax(bmx, __shfl_xor(bmx, off));
+        wmx = fmax(wmx, __shfl_xor(wmx, off));
+      }
+      if (lane == 0) {
+        double* rp = red + 5 * wave;
+        rp[0] = smin;
+        rp[1] = vmx;
+        rp[2] = amx;
+        rp[3] = bmx;
+        rp[4] = wmx;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        double v[5];
+        for (int q = 0; q < 5; ++q) {
+          v[q] = red[q];
+          for (int ww = 1; ww < kCheckW; ++ww) v[q] = q == 0 ? fmin(v[q], red[5 * ww]) : fmax(v[q], red[5 * ww + q]);
+        }
+        viol[sidx * 5 + 0] = c.a * (1.0 - sqrt(v[0]));
+        viol[sidx * 5 + 1] = c.vel_on ? sqrt(v[1]) - c.vmax : -DBL_MAX;
+        viol[sidx * 5 + 2] = c.acc_on ? sqrt(v[2]) - c.amax : -DBL_MAX;
+        viol[sidx * 5 + 3] = v[3];
+        viol[sidx * 5 + 4] = c.ws_on ? c.ws_a * (sqrt(v[4]) - 1.0) : 0.0;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+template <typename Tin, int D, int R>
+hipError_t launch_check(const CheckArgs& a) {
+  auto kern = f64_check_kernel<Tin, D, R>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)a.lds_bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(a.n_items), dim3(64 * kCheckW), a.lds_bytes, a.stream, a.cfgs, a.tab, a.a64, a.probs,
+                     a.items, a.n_items, static_cast<const Tin*>(a.xi), static_cast<const Tin*>(a.bvals), a.viol);
+  return hipGetLastError();
+}
+
 template <int D, int R, int W>
 hipError_t launch_instance(const F64Args& f, size_t lds, hipStream_t stream) {
   auto kern = f64_project_kernel<D, R, W>;
@@ -810,6 +1032,22 @@ int f64_waves(const DevCfg* const* cfgs, int n_cfgs, int R, int64_t n_items, int
     if (*lds <= kLds) return W;
   }
   return 0;
+}
+
+size_t f64_check_lds_bytes(const DevCfg& c, int R) { return (size_t)check_plan(c, R).total * sizeof(double); }
+
+hipError_t launch_f64_check(const CheckArgs& a, bool dbl, int D, int R) {
+  switch (D * 100 + R * 10 + (dbl ? 1 : 0)) {
+    case 210: return launch_check<float, 2, 1>(a);
+    case 211: return launch_check<double, 2, 1>(a);
+    case 220: return launch_check<float, 2, 2>(a);
+    case 221: return launch_check<double, 2, 2>(a);
+    case 310: return launch_check<float, 3, 1>(a);
+    case 311: return launch_check<double, 3, 1>(a);
+    case 320: return launch_check<float, 3, 2>(a);
+    case 321: return launch_check<double, 3, 2>(a);
+    default: return hipErrorNotSupported;
+  }
 }
 
 hipError_t launch_f64_project(const LaunchArgs& a, const double* a64, int D, int R, int W) {

@@ -70,3 +70,16 @@ def test_f64_non_finite_inputs():
         assert torch.equal(u.isnan(), v.isnan()) and bool(u[1].isnan().any()) and not bool(u[0].isnan().any())
         ok = ~v.isnan()
         _close(u[ok], v[ok], name)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_feasibility_matches_oracle(shape, prec):
+    """Violations from the matrix-core check against the oracle's, also where nothing collides or all do."""
+    from paper_2501_19042_amd import SafetyFilter
+    cfg, xb, bv, x0, _ = _inputs(*shape)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    x = x0.to(dt)[:40]
+    x[0] *= 0.01      # every pair inside the safety distance
+    v = SafetyFilter([cfg]).feasibility(x.cuda(), bv.to(dt).cuda(), precision=prec).cpu()
+    _close(v, O.feasibility(O.build_system(cfg), x.double(), bv.to(dt).double()), "violations")
