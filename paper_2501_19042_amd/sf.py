@@ -15,12 +15,17 @@ ProjectResult = namedtuple("ProjectResult", ["xi", "lam", "resid", "ckpt", "stat
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream_ptr(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # (the raw handle of the current stream, without a stream object: a small call is bound by the host)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+_ONE = ctypes.c_int32 * 1
 
 
 class Batch:
@@ -32,10 +37,10 @@ class Batch:
             raise ValueError("empty batch")
         P = len(entries)
         self.entries = entries
-        self._slots = (ctypes.c_int32 * P)(*[s for s, _ in entries])
-        self._counts = (ctypes.c_int32 * P)(*[c for _, c in entries])
-        self.c = N.SfBatch(P, ctypes.cast(self._slots, ctypes.POINTER(ctypes.c_int32)),
-                           ctypes.cast(self._counts, ctypes.POINTER(ctypes.c_int32)))
+        table = (ctypes.c_int32 * P) if P > 1 else _ONE
+        self._slots = table(*[s for s, _ in entries])
+        self._counts = table(*[c for _, c in entries])
+        self.c = N.SfBatch(P, self._slots, self._counts)
 
     @property
     def n_samples(self) -> int:
@@ -66,13 +71,14 @@ class SafetyFilter:
 
     # ---- sizes of a batch ---------------------------------------------------------
     def sizes(self, batch: Batch):
-        coef = bnd = 0
+        coef = bnd = samples = 0
         for slot, cnt in batch.entries:
             c = self.configs[slot]
-            per = c.n_robots * c.dims * (c.degree + 1)
-            coef += cnt * per
-            bnd += c.n_robots * c.dims * 6
-        return batch.n_samples, coef, bnd
+            rows = c.n_robots * c.dims
+            samples += cnt
+            coef += cnt * rows * (c.degree + 1)
+            bnd += rows * 6
+        return samples, coef, bnd
 
     def _batch(self, batch, xi_bar):
         if batch is None:
