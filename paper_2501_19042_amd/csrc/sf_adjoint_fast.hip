@@ -68,10 +68,10 @@ __host__ __device__ inline AdjLds adj_fast_plan(const DevCfg& c, int R, int KS, 
 }
 
 // Word of coefficient (robot, axis, kk) in a wave's partial back-projection, stored as the products leave it:
-// [axis][robot tile][r][lane], lane (col, grp) = (kk, robot 4 grp + r of the tile).
+// [axis][robot tile][r][lane], lane (col, grp) = (robot, coefficient grp + 4 r).
 template <int R>
 __device__ __forceinline__ int part_at(int robot, int d, int kk) {
-  return ((d * R + (robot >> 4)) * 4 + (robot & 3)) * 64 + ((robot & 15) >> 2) * 16 + kk;
+  return ((d * R + (robot >> 4)) * 4 + (kk >> 2)) * 64 + (kk & 3) * 16 + (robot & 15);
 }
 
 // Y[rr][d] = basis rows x coefficients for one tile: lane (col, grp) gets robot 16 rr + col at times 4 grp + r.
@@ -499,7 +499,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
                 const f4 cr = *cp;
                 *cp = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(cr[s], b4[s], gacc[rr][d]);
+                for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(b4[s], cr[s], gacc[rr][d]);
               }
           }
           wave_sync();
@@ -547,7 +547,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
               for (int d = 0; d < 3; ++d)
 #pragma unroll
-                for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(V[rr][d][s], b4[s], gacc[rr][d]);
+                for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(b4[s], V[rr][d][s], gacc[rr][d]);
             }
           }
         }
@@ -681,7 +681,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
               for (int d = 0; d < 3; ++d)
 #pragma unroll
-                for (int s = 0; s < 4; ++s) g[rr][d] = mfma4(v[rr][d][s], b4[s], g[rr][d]);
+                for (int s = 0; s < 4; ++s) g[rr][d] = mfma4(b4[s], v[rr][d][s], g[rr][d]);
           };
           f4 Y[R][3], D[R][3];
           tile_product<R, KS>(av, sxk, lane, Y);

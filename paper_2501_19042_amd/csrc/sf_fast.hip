@@ -10,31 +10,39 @@ static thread_local std::string g_fast_err;
 std::string fast_last_error() { return g_fast_err; }
 void fast_set_error(const char* msg) { g_fast_err = msg; }
 
-hipError_t fast_launch_single_p0_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int);
-hipError_t fast_launch_batched_p0_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
-                                     int);
-hipError_t fast_launch_single_p0_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int);
-hipError_t fast_launch_batched_p0_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
-                                     int);
-hipError_t fast_launch_single_p1_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int);
-hipError_t fast_launch_batched_p1_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
-                                     int);
-hipError_t fast_launch_single_p1_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int);
-hipError_t fast_launch_batched_p1_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
-                                     int);
-hipError_t fast_launch_single_p2_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int);
-hipError_t fast_launch_batched_p2_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
-                                     int);
-hipError_t fast_launch_single_p2_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int);
-hipError_t fast_launch_batched_p2_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*, const int*, const int*,
-                                     int);
+// launchers of the kernel instances, per operand precision, workspace flag and robot tiles
+typedef hipError_t SingleFn(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int W);
+typedef hipError_t ClassFn(const FastPlan&, const LaunchArgs&, const float*, const uint4*, int ci, int grid, int W);
+typedef hipError_t SegmentsFn(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+SingleFn fast_single_p0_w0_r1, fast_single_p0_w0_r2, fast_single_p0_w1_r1, fast_single_p0_w1_r2;
+SingleFn fast_single_p1_w0_r1, fast_single_p1_w0_r2, fast_single_p1_w1_r1, fast_single_p1_w1_r2;
+SingleFn fast_single_p2_w0_r1, fast_single_p2_w0_r2, fast_single_p2_w1_r1, fast_single_p2_w1_r2;
+ClassFn fast_class_p0_w0_r1, fast_class_p0_w0_r2, fast_class_p0_w1_r1, fast_class_p0_w1_r2;
+ClassFn fast_class_p1_w0_r1, fast_class_p1_w0_r2, fast_class_p1_w1_r1, fast_class_p1_w1_r2;
+ClassFn fast_class_p2_w0_r1, fast_class_p2_w0_r2, fast_class_p2_w1_r1, fast_class_p2_w1_r2;
+SegmentsFn fast_segments_p0_w0_r1, fast_segments_p0_w0_r2, fast_segments_p0_w1_r1, fast_segments_p0_w1_r2;
+SegmentsFn fast_segments_p1_w0_r1, fast_segments_p1_w0_r2, fast_segments_p1_w1_r1, fast_segments_p1_w1_r2;
+SegmentsFn fast_segments_p2_w0_r1, fast_segments_p2_w0_r2, fast_segments_p2_w1_r1, fast_segments_p2_w1_r2;
+// [fp32, bf16, fp16][workspace][robot tiles - 1]
+static SingleFn* const kSingle[3][2][2] = {
+    {{fast_single_p0_w0_r1, fast_single_p0_w0_r2}, {fast_single_p0_w1_r1, fast_single_p0_w1_r2}},
+    {{fast_single_p1_w0_r1, fast_single_p1_w0_r2}, {fast_single_p1_w1_r1, fast_single_p1_w1_r2}},
+    {{fast_single_p2_w0_r1, fast_single_p2_w0_r2}, {fast_single_p2_w1_r1, fast_single_p2_w1_r2}}};
+static ClassFn* const kClass[3][2][2] = {
+    {{fast_class_p0_w0_r1, fast_class_p0_w0_r2}, {fast_class_p0_w1_r1, fast_class_p0_w1_r2}},
+    {{fast_class_p1_w0_r1, fast_class_p1_w0_r2}, {fast_class_p1_w1_r1, fast_class_p1_w1_r2}},
+    {{fast_class_p2_w0_r1, fast_class_p2_w0_r2}, {fast_class_p2_w1_r1, fast_class_p2_w1_r2}}};
+static SegmentsFn* const kSegments[3][2][2] = {
+    {{fast_segments_p0_w0_r1, fast_segments_p0_w0_r2}, {fast_segments_p0_w1_r1, fast_segments_p0_w1_r2}},
+    {{fast_segments_p1_w0_r1, fast_segments_p1_w0_r2}, {fast_segments_p1_w1_r1, fast_segments_p1_w1_r2}},
+    {{fast_segments_p2_w0_r1, fast_segments_p2_w0_r2}, {fast_segments_p2_w1_r1, fast_segments_p2_w1_r2}}};
 
-hipError_t fast_launch_segments_p0_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
-hipError_t fast_launch_segments_p0_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
-hipError_t fast_launch_segments_p1_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
-hipError_t fast_launch_segments_p1_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
-hipError_t fast_launch_segments_p2_w0(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
-hipError_t fast_launch_segments_p2_w1(const FastPlan&, const LaunchArgs&, const float*, const uint4*);
+// Resets the queue heads of a launch sequence (a kernel node rather than a memset, so the
+// sequence can be captured in a graph).
+static __global__ void reset_queue_kernel(int* queue, int n) {
+  if (threadIdx.x == 0 && blockIdx.x == 0)
+    for (int i = 0; i < n; ++i) queue[i] = 0;
+}
 
 using fastk::fast_lds_plan;
 using fastk::waves_per_simd;
@@ -81,16 +89,16 @@ void a32_fill(const DevCfg& c, const double* P3, float* out) {
   for (int tau = 0; tau < NT; ++tau)
     for (int b = 0; b < 3; ++b)
       for (int lane = 0; lane < 64; ++lane) {
-        const int col = lane & 15, grp = lane >> 4;
+        const int col = lane & 15, grp = lane >> 4, kr = fastk::coef_of_row(col);
         // S1: P[t = 16 tau + col][k = 4 s + grp], times past the horizon repeat the last grid time (so
         // every row of the product is a real point of the trajectory); S4: zero past the horizon
         float* a = out + ((((size_t)tau * 3 + b) * 2 + 0) * 64 + lane) * 4;
-        float* bq = out + ((((size_t)tau * 3 + b) * 2 + 1) * 64 + lane) * 4;  // S4: rho P[t = 16 tau + 4 grp + s][k = col]
+        float* bq = out + ((((size_t)tau * 3 + b) * 2 + 1) * 64 + lane) * 4;  // S4: rho P[t = 16 tau + 4 grp + s][k of row col]
         for (int s = 0; s < 4; ++s) {
           const int t = std::min(16 * tau + col, c.H - 1), k = 4 * s + grp;
           a[s] = k < c.m ? (float)P3[((size_t)b * c.H + t) * c.m + k] : 0.0f;
           const int t4 = 16 * tau + 4 * grp + s;
-          bq[s] = (t4 < c.H && col < c.m) ? (float)(rho[b] * P3[((size_t)b * c.H + t4) * c.m + col]) : 0.0f;
+          bq[s] = (t4 < c.H && kr < c.m) ? (float)(rho[b] * P3[((size_t)b * c.H + t4) * c.m + kr]) : 0.0f;
         }
       }
 }
@@ -134,7 +142,7 @@ double item_cost(const DevCfg& c, int count) {
 }  // namespace
 
 bool fast_cfg_covered(const DevCfg& c) {
-  return cfg_supported(c) && (size_t)fast_lds_plan(c, c.n <= 16 ? 1 : 2, 4, 1).total * 4 <= 160 * 1024;
+  return cfg_supported(c) && (size_t)fast_lds_plan(c, c.n <= 16 ? 1 : 2, 4, 4, 1).total * 4 <= 160 * 1024;
 }
 
 sf_status fast_plan_build(const std::vector<DevCfg>& cfgs, const std::vector<DevProblem>& probs,
@@ -149,7 +157,7 @@ sf_status fast_plan_build(const std::vector<DevCfg>& cfgs, const std::vector<Dev
     if (used[q]) first = (int)q;
   if (first < 0) return SF_OK;
   bool mixed = false;
-  int maxKS = 2, maxNT = 1;
+  int maxKS = 2;
   for (size_t q = 0; q < probs.size(); ++q) {
     if (!used[q]) continue;
     const DevProblem& p = probs[q];
@@ -158,11 +166,14 @@ sf_status fast_plan_build(const std::vector<DevCfg>& cfgs, const std::vector<Dev
     if (p.cfg != probs[first].cfg) mixed = true;
     if (c.ws_on) out.ws = true;
     maxKS = std::max(maxKS, (c.m + 3) / 4);
-    maxNT = std::max(maxNT, (c.H + 15) / 16);
+  }
+  for (size_t q = 0; q < probs.size(); ++q) {
+    if (!used[q]) continue;
+    const DevCfg& c = cfgs[probs[q].cfg];
     for (int wi = 0; wi < 3; ++wi)
       for (int mp = 0; mp < 3; ++mp)
         out.lds_bytes[wi][mp] = std::max(out.lds_bytes[wi][mp],
-                                         (size_t)fast_lds_plan(c, c.n <= 16 ? 1 : 2, wi + 2, mp).total * 4);
+                                         (size_t)fast_lds_plan(c, c.n <= 16 ? 1 : 2, maxKS, wi + 2, mp).total * 4);
   }
   if (out.lds_bytes[2][1] > 160 * 1024) return SF_OK;
   const DevCfg& c0 = cfgs[probs[first].cfg];
@@ -224,7 +235,7 @@ sf_status fast_plan_build(const std::vector<DevCfg>& cfgs, const std::vector<Dev
         const DevCfg& c = cfgs[probs[items[o.second].problem].cfg];
         for (int wi = 0; wi < 3; ++wi)
           for (int mp = 0; mp < 3; ++mp)
-            C.lds_bytes[wi][mp] = std::max(C.lds_bytes[wi][mp], (size_t)fast_lds_plan(c, C.R, wi + 2, mp).total * 4);
+            C.lds_bytes[wi][mp] = std::max(C.lds_bytes[wi][mp], (size_t)fast_lds_plan(c, C.R, maxKS, wi + 2, mp).total * 4);
       }
       const int per_cu = std::max(1, std::min(4, (int)((160 * 1024) / std::max<size_t>(C.lds_bytes[wdef - 2][0], 1))));
       C.grid = std::min(C.n_items, out.ncu * per_cu);
@@ -251,24 +262,26 @@ void fast_plan_free(FastPlan& p) {
   p.ok = false;
 }
 
+// Row of the instance tables for a precision; -1: none.
+static int instance_row(int precision) {
+  if (precision >= SF_FP32 && precision <= SF_FP16) return precision - SF_FP32;
+  g_fast_err = "precision not implemented in the MFMA kernels";
+  return -1;
+}
+
+// The queue heads are reset, then each class selected by cls_mask runs with its own waves per workgroup W[c]
+// and workgroup count grid[c] (0 = the class's default).
 hipError_t fast_launch_batched(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,
                                int precision, const int* grid, const int* W, int cls_mask) {
-  const uint4* t = static_cast<const uint4*>(a16);
-  const bool ws = p.ws;
-  switch (precision) {
-    case SF_FP32:
-      return ws ? fast_launch_batched_p0_w1(p, a, tab32, t, grid, W, cls_mask)
-                : fast_launch_batched_p0_w0(p, a, tab32, t, grid, W, cls_mask);
-    case SF_BF16:
-      return ws ? fast_launch_batched_p1_w1(p, a, tab32, t, grid, W, cls_mask)
-                : fast_launch_batched_p1_w0(p, a, tab32, t, grid, W, cls_mask);
-    case SF_FP16:
-      return ws ? fast_launch_batched_p2_w1(p, a, tab32, t, grid, W, cls_mask)
-                : fast_launch_batched_p2_w0(p, a, tab32, t, grid, W, cls_mask);
-    default:
-      g_fast_err = "precision not implemented in the MFMA kernels";
-      return hipErrorNotSupported;
+  const int mp = instance_row(precision);
+  if (mp < 0) return hipErrorNotSupported;
+  hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, a.stream, p.d_queue, p.n_cls);
+  for (int ci = 0; ci < p.n_cls; ++ci) {
+    if (!(cls_mask & (1 << ci))) continue;
+    const hipError_t e = kClass[mp][p.ws][p.cls[ci].R - 1](p, a, tab32, static_cast<const uint4*>(a16), ci, grid[ci], W[ci]);
+    if (e != hipSuccess) return e;
   }
+  return hipSuccess;
 }
 
 hipError_t fast_launch(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16, int precision) {
@@ -287,29 +300,16 @@ hipError_t fast_launch(const FastPlan& p, const LaunchArgs& a, const float* tab3
 
 hipError_t fast_launch_segments(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,
                                 int precision) {
-  const uint4* t = static_cast<const uint4*>(a16);
-  switch (precision) {
-    case SF_FP32: return p.ws ? fast_launch_segments_p0_w1(p, a, tab32, t) : fast_launch_segments_p0_w0(p, a, tab32, t);
-    case SF_BF16: return p.ws ? fast_launch_segments_p1_w1(p, a, tab32, t) : fast_launch_segments_p1_w0(p, a, tab32, t);
-    case SF_FP16: return p.ws ? fast_launch_segments_p2_w1(p, a, tab32, t) : fast_launch_segments_p2_w0(p, a, tab32, t);
-    default:
-      g_fast_err = "precision not implemented in the MFMA kernels";
-      return hipErrorNotSupported;
-  }
+  const int mp = instance_row(precision);
+  if (mp < 0) return hipErrorNotSupported;
+  return kSegments[mp][p.ws][p.R - 1](p, a, tab32, static_cast<const uint4*>(a16));
 }
 
 hipError_t fast_launch_single(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,
                               int precision, int W) {
-  const uint4* t = static_cast<const uint4*>(a16);
-  const bool ws = p.ws;
-  switch (precision) {
-    case SF_FP32: return ws ? fast_launch_single_p0_w1(p, a, tab32, t, W) : fast_launch_single_p0_w0(p, a, tab32, t, W);
-    case SF_BF16: return ws ? fast_launch_single_p1_w1(p, a, tab32, t, W) : fast_launch_single_p1_w0(p, a, tab32, t, W);
-    case SF_FP16: return ws ? fast_launch_single_p2_w1(p, a, tab32, t, W) : fast_launch_single_p2_w0(p, a, tab32, t, W);
-    default:
-      g_fast_err = "precision not implemented in the MFMA kernels";
-      return hipErrorNotSupported;
-  }
+  const int mp = instance_row(precision);
+  if (mp < 0) return hipErrorNotSupported;
+  return kSingle[mp][p.ws][p.R - 1](p, a, tab32, static_cast<const uint4*>(a16), W);
 }
 
 }  // namespace sf

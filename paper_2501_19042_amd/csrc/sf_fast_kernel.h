@@ -15,13 +15,19 @@
 //         listed pair-times are projected and scattered into an LDS accumulator.
 //     S4  g += P_b^T (rho_b R_b) as MFMA products, only for tiles with a nonzero residual; the
 //         S1 output layout is exactly the A-operand layout this product needs.
-//   barrier; tail (the 3 x 16R robot-axis rows, two lanes per row where they fit)
-//     multiplier step and the structured QP step of eq. (xi_step) on the free coefficients.
+//   barrier; tail (one wave per axis): multiplier step, and the structured QP step of eq. (xi_step) on the
+//     free coefficients.
 //   barrier
 //
-// This header holds the kernels and their launchers; sf_fast_p<MP>_w<WS>.hip instantiate them per
-// operand precision and workspace flag (so the instances compile in parallel), sf_fast.hip holds
-// the host side (operand tables, plans, dispatch).
+// The state is stored [axis][coefficient][16R robots], and lane (col, grp) of the S1 and S4 products and of the
+// tail covers robot col and coefficients grp, grp + 4, ...: the S4 product, its basis operand's rows permuted
+// (coef_of_row), leaves its result with the lanes that own it in the tail, so it is stored and summed without
+// address arithmetic or bank conflicts.
+//
+// This header holds the kernels and their launchers; sf_fast_p<MP>_w<WS>[_r2].hip instantiate them per
+// operand precision, workspace flag and robot tiles (so the instances compile in parallel, and the register
+// allocation of one does not depend on the others: with the two-tile kernels in the same source the one-tile
+// kernels spilled 19 registers), sf_fast.hip holds the host side (operand tables, plans, dispatch).
 #pragma once
 
 #include "sf_fast.h"
@@ -61,15 +67,16 @@ __device__ __forceinline__ f4 mfma16(f16x8 a, f16x8 b, f4 c) {
 // coefficients 8 (grp & 1) .. + 7 of robot col.  First instruction: grp 0, 1 carry xi_hi against
 // P_hi and grp 2, 3 carry xi_hi against P_lo; second instruction: grp 0, 1 carry xi_lo against
 // P_hi, grp 2, 3 are zero.  The sum is P_hi xi_hi + P_lo xi_hi + P_hi xi_lo in fp32: the
-// rounding residuals of both factors are fed back as correction terms.
+// rounding residuals of both factors are fed back as correction terms.  x: coefficient 0 of the robot's row,
+// `step` words apart.
 template <int MP>
-__device__ __forceinline__ void split_xi(const float* x, int robot, int n, int m, int d, int grp,
+__device__ __forceinline__ void split_xi(const float* x, int step, bool real, int m, int grp,
                                          typename Half<MP>::V& b1, typename Half<MP>::V& b2) {
   typedef typename Half<MP>::E E;
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
     const int k = 8 * (grp & 1) + v;
-    const float xv = (robot < n && k < m) ? x[(robot * 3 + d) * m + k] : 0.0f;
+    const float xv = (real && k < m) ? x[k * step] : 0.0f;
     const E hi = static_cast<E>(xv);
     const E lo = static_cast<E>(xv - static_cast<float>(hi));
     b1[v] = hi;
@@ -94,9 +101,10 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 // accumulator Ct as [axis][robot (16R)][time] with 16-word rows whose four 16-byte chunks are
 // XOR-swizzled by the robot index (tile_at), so that the 16-byte accesses of 16 consecutive lanes
 // hit distinct banks; boxes bb [robot][box_row(R)]; per tile, the list of pairs that can collide.  Once
-// its time tiles are done, a wave reuses its own region for its partial back-projection (nDm
-// words) and, after the final residual pass, for its partial sums.
-constexpr int kQPCols = 16;              // QP matrix row in LDS: both halves, each padded (m_f <= 10)
+// its time tiles are done, a wave reuses its own region for its partial back-projection (3 x 16R x 16
+// words, as the products leave it) and, after the final residual pass, for its partial sums.
+// Coefficient of row i of the S4 product's result: lane group i / 4 holds it in register i % 4.
+__host__ __device__ constexpr int coef_of_row(int i) { return (i >> 2) + 4 * (i & 3); }
 // Row strides (words) chosen so that the 16-byte accesses of 16 consecutive robots hit 16
 // distinct groups of 4 banks (64 banks): boxes (lo xyz _, hi xyz _, pad) and 16-bit operands.  The
 // forward kernel with two robot tiles keeps its boxes unpadded (two-way conflicts in the broad
@@ -118,8 +126,10 @@ __device__ __forceinline__ int hb_at(int row, int e) {
   if constexpr (R == 2) return row * 32 + (e ^ (((row >> 2) & 3) << 3));
   else return row * (2 * kHBRow) + e;
 }
+// QP matrix row in LDS: the free coefficients of up to 4 KS in all, padded to whole 16-byte chunks.
+__host__ __device__ constexpr int qp_row(int KS) { return (4 * KS - 6 + 3) & ~3; }
 struct FastLds {
-  int xi, lam, xb, xprev, dbar, corr, pairs, vmx, amx, wmx, dxi, cmx, qp, hb, tiles, per_wave, total;
+  int xi, lam, xb, xprev, corr, pairs, mx, dxi, cm, qp, hb, tiles, per_wave, total;
   int xt, ct, bb, plist;   // offsets inside one wave's tile region
 };
 // Pair table and pair lists of a wave's tiles (count, then pair codes i | j << 8) per tile: 32-bit
@@ -131,28 +141,22 @@ template <int R> struct PairList { typedef int T; };
 __host__ __device__ constexpr int box_at(int q, int nr) { return (((q * plist_entries(nr) + 1) >> 1) + 3) & ~3; }
 template <> struct PairList<2> { typedef uint16_t T; };
 
-__host__ __device__ inline FastLds fast_lds_plan(const DevCfg& c, int R, int W, int MP) {
-  const int nDm = c.n * 3 * c.m, nDf = c.n * 3 * c.mf;
-  const int nr = 16 * R, Npmax = nr * (nr - 1) / 2;
+__host__ __device__ inline FastLds fast_lds_plan(const DevCfg& c, int R, int KS, int W, int MP) {
+  const int nr = 16 * R, Npmax = nr * (nr - 1) / 2, nDm = 3 * c.m * nr;
   FastLds p;
   int o = 0;
-  // (two robot tiles: the previous iterate of the final residual lives in xi_out and the first-step
-  // correction is folded into xi_bar for step 0, so neither takes LDS)
-  p.xi = o; o += nDm;
+  // (two robot tiles: the previous iterate of the final residual lives in xi_out)
+  p.xi = o; o += nDm;                      // [axis][coefficient][16R robots], zero past the swarm
   p.lam = o; o += nDm;
-  p.xb = o; o += nDm;
+  p.xb = o; o += nDm;                      // (two robot tiles: with the first-step correction for step 0)
   p.xprev = o; o += R == 1 ? nDm : 0;
-  p.dbar = o; o += 3 * kNFix;
-  p.corr = o; o += R == 1 ? nDf : 0;
+  p.corr = o; o += R == 1 ? 3 * c.mf * nr : 0;   // first-step correction [axis][f][16R robots]
   p.pairs = o; o += R == 2 ? 0 : Npmax;  // (two robot tiles: in the pair-list regions)
-  p.vmx = o; o += W * nr;                  // per wave and robot: max ||v||^2 over the wave's tiles
-  p.amx = o; o += W * nr;                  // same for the acceleration
-  p.dxi = o; o += 3 * nr;                  // per (robot, axis): max |change| of a free coefficient
-  p.cmx = o; o += 3 * nr;                  // per (robot, axis): max |coefficient| of the iterate
+  p.mx = o; o += 2 * 3 * nr;               // [evaluation parity][v, a, workspace][robot]: largest squares
+  p.dxi = o; o += 3 * nr;                  // per (axis, robot): max |change| of a free coefficient
+  p.cm = o; o += 3 * 64;                   // per axis and tail lane: max |coefficient| over the iterates
   o = (o + 3) & ~3;
-  // X1, X01 transposed: rows of at most kQPCols floats, or of 4 QC <= 12 floats in the layout of
-  // one robot tile with three waves (QC = 16-byte chunks of the free coefficients)
-  p.qp = o; o += 2 * c.mf * (R == 1 && W == 3 ? 12 : kQPCols);
+  p.qp = o; o += 2 * c.mf * qp_row(KS);    // X1, X01: rows of free coefficients, zero-padded
   o = (o + 3) & ~3;
   p.hb = o; o += MP ? 3 * nr * hb_row(R) : 0; // 16-bit S1 B operands: [axis][robot][hi x16, lo x16 (, pad)]
   o = (o + 3) & ~3;                        // 16-byte alignment of the tile buffers
@@ -163,13 +167,10 @@ __host__ __device__ inline FastLds fast_lds_plan(const DevCfg& c, int R, int W, 
   p.bb = R == 2 ? 0 : 6 * nr * 16;
   p.plist = R == 2 ? 6 * nr * 16 : p.bb + box_row(R) * nr;   // per tile of the wave: [count, pairs...] kept across iterations
   const int NT = (c.H + 15) / 16, TQ = (NT + W - 1) / W;
-  int pw = p.plist + (R == 2 ? (TQ * plist_entries(nr) + 1) / 2 + 12 : TQ * plist_entries(nr));
-  if (pw < nDm) pw = nDm;
-  if (pw < 128) pw = 128;
+  const int pw = p.plist + (R == 2 ? (TQ * plist_entries(nr) + 1) / 2 + 12 : TQ * plist_entries(nr));
   p.per_wave = (pw + 3) & ~3;
   p.tiles = o;
   o += W * p.per_wave;
-  p.wmx = o; o += c.ws_on ? W * nr : 0;    // per wave and robot: max ||M_w^{-1} (p - p_w)||^2 (workspace)
   p.total = o;
   return p;
 }
@@ -292,21 +293,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
   const int rw = fpr ? 3 : 2;            // resid_out columns
   constexpr int NR = 16 * R;
   constexpr int PR = (NR * (NR - 1) / 2 + 63) / 64;   // 64-pair rounds of the broad phase
-  constexpr int MFX = 4 * KS - 6;                     // free coefficients per robot-axis, at most
-  constexpr int HALVES = 6 * NR <= 64 * W ? 2 : 1;    // lanes per row in the multiplier/QP step
-  constexpr int FH = (MFX + HALVES - 1) / HALVES;     // free coefficients per lane
-  constexpr int FHP = (FH + 3) & ~3;                  // ... padded to whole 16-byte chunks
-  static_assert(HALVES * FHP <= kQPCols, "QP matrix rows");
-  constexpr int TAILW = (3 * NR * HALVES + 63) / 64;  // waves running the multiplier and QP steps
-  // One robot tile and three waves: wave a runs axis a of the multiplier/QP step with four lanes per
-  // row (robot, a), so every wave shares it.
-  constexpr bool QUART = R == 1 && W == 3;
-  constexpr int FQ = (MFX + 3) / 4;                   // free coefficients per lane in that layout
-  constexpr int QC = (MFX + 3) / 4;                   // 16-byte chunks of a QP matrix row
-  static_assert(!QUART || 4 * QC <= 12, "QP matrix rows of the quarter layout");
   // two robot tiles: no LDS copy of the previous iterate or of the first-step correction (see the plan)
   constexpr bool LEAN = R == 2;
-  static_assert(TAILW <= W, "the multiplier/QP step needs 3 x 16R lanes");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nthr = 64 * W;
   {
@@ -319,9 +307,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
     const WorkItem w = items[it];
     const DevProblem pr = probs[w.problem];
     const DevCfg c = cfgs[pr.cfg];
-    const FastLds L = fast_lds_plan(c, R, W, MP);
+    const FastLds L = fast_lds_plan(c, R, KS, W, MP);
     const int n = c.n, m = c.m, mf = c.mf, H = c.H;
-    const int nDm = n * 3 * m, nDf = n * 3 * mf;
+    const int nDm = n * 3 * m, nDf = n * 3 * mf, nRm = 3 * m * NR;
     const int Np = n * (n - 1) / 2;
     const int NT = (H + 15) / 16;
     const int TQ = (NT + W - 1) / W;            // time tiles per wave
@@ -342,7 +330,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
     float* slam = smem + L.lam;
     float* sxb = smem + L.xb;
     float* sxprev = smem + L.xprev;
-    float* sdbar = smem + L.dbar;
+    float* sdbar = smem + L.tiles;         // (set-up only)
     float* scorr = smem + L.corr;
     // pair table, lexicographic (i, j), i < j: shared with one robot tile; with two, each wave's copy
     // in its pair-list region, written where needed (set-up, final residual)
@@ -354,11 +342,19 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         for (int j = i + 1; j < n; ++j) spairs[p++] = static_cast<PT>(i | (j << 8));
       }
     };
-    float* s_vmx = smem + L.vmx;
-    float* s_amx = smem + L.amx;
+    // largest squares of the evaluated rows, as bits (non-negative floats order like their bits); the buffer
+    // of one evaluation is read by the next iteration and cleared in its tail
+    uint32_t* s_mx = reinterpret_cast<uint32_t*>(smem + L.mx);
     float* s_dxi = smem + L.dxi;
-    float* s_cmx = smem + L.cmx;
-    float* s_wmx = smem + L.wmx;
+    float* s_cm = smem + L.cm;
+    // LDS word of element q of a sample ([robot][axis][coefficient]); the division by m <= 16 is exact for
+    // the q < 1536 of a sample
+    const unsigned minv = (65535u + m) / m;
+    auto state_at = [&](int q) {
+      const int row = (int)(((unsigned)q * minv) >> 16), robot = row / 3;
+      return ((row - 3 * robot) * m + (q - row * m)) * NR + robot;
+    };
+    auto coef_at = [&](int robot, int d, int kk) { return (d * m + kk) * NR + robot; };
     // 16-bit hi/lo split of xi in the S1 B-operand layout, kept current by whoever writes xi
     typedef typename Half<MP == 0 ? 1 : MP>::E HE;
     HE* shb = reinterpret_cast<HE*>(smem + L.hb);
@@ -382,23 +378,14 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
 
     if constexpr (R == 2) fill_pairs(tid & 63, 64);
     else fill_pairs(tid, nthr);
-    // QP matrices X1 (relative motion) and X01 (mean motion minus relative), transposed and cut
-    // into the halves of the outputs the lanes own: [matrix][half][f2][j] = X[half * FH + j][f2]
-    // (zero-padded)
+    // QP matrices X1 (relative motion) and X01 (mean motion minus relative), [matrix][f][f2] (zero-padded)
+    constexpr int QR = qp_row(KS), MFX = 4 * KS - 6;   // (MFX: free coefficients per robot-axis, at most)
     float* sX1 = smem + L.qp;
-    if constexpr (QUART) {
-      // [matrix][f][f2], rows of 4 QC floats (zero-padded)
-      for (int q = tid; q < 2 * mf * 4 * QC; q += nthr) {
-        const int c4 = q % (4 * QC), f = (q / (4 * QC)) % mf, mat = q / (4 * QC * mf);
-        sX1[q] = c4 < mf ? (mat == 0 ? X1 : X01)[f * mf + c4] : 0.0f;
-      }
-    } else {
-      for (int q = tid; q < 2 * HALVES * mf * FHP; q += nthr) {
-        const int j = q % FHP, f2 = (q / FHP) % mf, mh = q / (FHP * mf);
-        const int h = mh % HALVES, mat = mh / HALVES, f = h * FH + j;
-        sX1[q] = (j < FH && f < mf) ? (mat == 0 ? X1 : X01)[f * mf + f2] : 0.0f;
-      }
+    for (int q = tid; q < 2 * mf * QR; q += nthr) {
+      const int f2 = q % QR, f = (q / QR) % mf, mat = q / (QR * mf);
+      sX1[q] = f2 < mf ? (mat == 0 ? X1 : X01)[f * mf + f2] : 0.0f;
     }
+    for (int q = tid; q < nRm; q += nthr) sxi[q] = slam[q] = sxb[q] = 0.0f;   // (phantom robots stay zero)
     // basis operand tables: fp32 [tile][basis][S1 A operand, S4 B operand (x rho)][lane],
     // 16-bit [tile][basis][instruction][lane]
     const float4* a32c = reinterpret_cast<const float4*>(a16) + c.off_a32;
@@ -418,31 +405,34 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
       const int64_t sidx = pr.sample_base + sl;
       for (int q = tid; q < nDm; q += nthr) {
         const float x = xi_bar[coef + q];
-        sxb[q] = x;
-        sxi[q] = xi0 ? xi0[coef + q] : x;
-        slam[q] = lam0 ? lam0[coef + q] : 0.0f;
+        const int e = state_at(q);
+        sxb[e] = x;
+        sxi[e] = xi0 ? xi0[coef + q] : x;
+        slam[e] = lam0 ? lam0[coef + q] : 0.0f;
       }
       for (int q = tid; q < 3 * NR; q += nthr) s_dxi[q] = 0.0f;
+      for (int q = tid; q < 2 * 3 * NR; q += nthr) s_mx[q] = 0u;
       for (int q = lane; q < 3 * NR * 16; q += 64) Ct[q] = 0.0f;
       // a sample the input check flagged (non-finite input) is not iterated; the status pass then
       // writes NaN over its outputs
       const int32_t in_flag = status_out ? __builtin_amdgcn_readfirstlane(status_out[sidx]) : 0;
       const int iters_s = in_flag < 0 ? 0 : iters;
       __syncthreads();
-      // per-row bound on |coefficient| over the iterates: the initial one and the pinned values
-      for (int q = tid; q < 3 * NR; q += nthr) {
-        float cm = 0.0f;
-        if (q < 3 * n) {
-          for (int kk = 0; kk < m; ++kk) cm = fmaxf(cm, fabsf(sxi[q * m + kk]));
-          for (int r = 0; r < kNFix; ++r) cm = fmaxf(cm, fabsf(pinned(q, r)));
+      // bound on |coefficient| over the iterates: the initial one and the pinned values
+      for (int q = tid; q < 3 * 64; q += nthr) {
+        const int d = q >> 6, rb = q & 15, q4 = (q >> 4) & 3;
+        float cmx = 0.0f;
+        for (int robot = rb; robot < n; robot += 16) {
+          for (int kk = q4; kk < m; kk += 4) cmx = fmaxf(cmx, fabsf(sxi[coef_at(robot, d, kk)]));
+          for (int r = q4; r < kNFix; r += 4) cmx = fmaxf(cmx, fabsf(pinned(robot * 3 + d, r)));
         }
-        s_cmx[q] = cm;
+        s_cm[q] = cmx;
       }
       if constexpr (MP != 0) {
         // one thread per (axis, robot, coefficient) of the padded operand rows (zeros outside)
         for (int q = tid; q < 3 * NR * 16; q += nthr) {
           const int row = q >> 4, kk = q & 15, d = row / NR, robot = row - d * NR;
-          put_split(robot, d, kk, (robot < n && kk < m) ? sxi[(robot * 3 + d) * m + kk] : 0.0f);
+          put_split(robot, d, kk, (robot < n && kk < m) ? sxi[coef_at(robot, d, kk)] : 0.0f);
         }
       }
       // the first QP step also moves the pinned coefficients (from xi0 to their boundary values);
@@ -450,20 +440,20 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
       for (int q = tid; q < 3 * kNFix; q += nthr) {
         const int d = q / kNFix, r = q - d * kNFix;
         float s = 0.0f;
-        for (int i = 0; i < n; ++i) s += sxi[(i * 3 + d) * m + fixed_k(r)] - pinned(i * 3 + d, r);
+        for (int i = 0; i < n; ++i) s += sxi[coef_at(i, d, fixed_k(r))] - pinned(i * 3 + d, r);
         sdbar[q] = s * inv_n;
       }
       __syncthreads();
       for (int q = tid; q < nDf; q += nthr) {
-        const int row = q / mf, f = q - row * mf, d = row % 3;
+        const int row = q / mf, f = q - row * mf, robot = row / 3, d = row - 3 * robot;
         float acc = 0.0f;
         for (int r = 0; r < kNFix; ++r) {
-          const float dl = sxi[row * m + fixed_k(r)] - pinned(row, r);
+          const float dl = sxi[coef_at(robot, d, fixed_k(r))] - pinned(row, r);
           acc = fmaf(n_rho_c * Gfx[f * kNFix + r], dl - sdbar[d * kNFix + r], acc);
           acc = fmaf(Rfx[f * kNFix + r], dl, acc);
         }
-        if constexpr (LEAN) sxb[row * m + 3 + f] += acc;   // step 0 reads xi_bar + correction
-        else scorr[q] = acc;
+        if constexpr (LEAN) sxb[coef_at(robot, d, 3 + f)] += acc;   // step 0 reads xi_bar + correction
+        else scorr[(d * mf + f) * NR + robot] = acc;
       }
       __syncthreads();
       // bound-ball drift tracking, lane = robot, identical in every wave: margin to the bound at
@@ -494,56 +484,47 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         if (ckpt && (k % ckpt_every) == 0) {
           const int64_t base = (int64_t)(k / ckpt_every) * 2 * ckpt_stride + coef;
           for (int q = tid; q < nDm; q += nthr) {
-            ckpt[base + q] = sxi[q];
-            ckpt[base + ckpt_stride + q] = slam[q];
+            const int e = state_at(q);
+            ckpt[base + q] = sxi[e];
+            ckpt[base + ckpt_stride + q] = slam[e];
           }
         }
-        if ((resid_out || status_out) && k == iters_s - 1)
-          for (int q = tid; q < nDm; q += nthr) {
-            if constexpr (LEAN) xi_out[coef + q] = sxi[q];   // overwritten with the result at the end
-            else sxprev[q] = sxi[q];
-          }
+        if ((resid_out || status_out) && k == iters_s - 1) {
+          if constexpr (LEAN)   // overwritten with the result at the end
+            for (int q = tid; q < nDm; q += nthr) xi_out[coef + q] = sxi[state_at(q)];
+          else
+            for (int q = tid; q < nRm; q += nthr) sxprev[q] = sxi[q];
+        }
         // Velocity/acceleration at every grid time move by at most L * ||max_k |d xi_{i,d,k}| ||_2
         // per step (L = max_t sum_k |basis row|).  While the accumulated drift of every robot stays
         // below its margin to the bound at the last evaluation, the ball residuals are exactly zero
         // and S1/S3/S4 for that basis are skipped.  Iterations 0 and 1 always evaluate (the pinned
         // coefficients change in the first step).
+        const int par = k & 1;
+        const bool clear_mx = (prev_eval | ws_prev) != 0;   // the other buffer holds the last evaluation
         int eval_flags = 3;
-        float cm;   // bound on |coefficient| of robot `lane` over the iterates so far
         {
           float dn = 0.0f;
-          cm = 0.0f;
           if (lane < n) {
             // margins to the bounds measured by the previous iteration if it evaluated them
             // (every wave computes the same values).  The hardware square root (1 ulp) serves: the
             // test below keeps a 1e-4 relative slack, far above its error.
+            const uint32_t* pm = s_mx + (par ^ 1) * 3 * NR + lane;
             if (prev_eval & 1) {
-              float mx = 0.0f;
-#pragma unroll
-              for (int ww = 0; ww < W; ++ww) mx = fmaxf(mx, s_vmx[ww * NR + lane]);
-              mv = vmax - __builtin_amdgcn_sqrtf(mx);
+              mv = vmax - __builtin_amdgcn_sqrtf(__uint_as_float(pm[0]));
               dv = 0.0f;
             }
             if (prev_eval & 2) {
-              float mx = 0.0f;
-#pragma unroll
-              for (int ww = 0; ww < W; ++ww) mx = fmaxf(mx, s_amx[ww * NR + lane]);
-              ma = amax - __builtin_amdgcn_sqrtf(mx);
+              ma = amax - __builtin_amdgcn_sqrtf(__uint_as_float(pm[NR]));
               da = 0.0f;
             }
-            const float d0 = s_dxi[lane * 3], d1 = s_dxi[lane * 3 + 1], d2 = s_dxi[lane * 3 + 2];
-            cm = fmaxf(fmaxf(s_cmx[lane * 3], s_cmx[lane * 3 + 1]), s_cmx[lane * 3 + 2]);
+            const float d0 = s_dxi[lane], d1 = s_dxi[NR + lane], d2 = s_dxi[2 * NR + lane];
             dn = __builtin_amdgcn_sqrtf(d0 * d0 + d1 * d1 + d2 * d2);
             px_ += d0;
             py_ += d1;
             pz_ += d2;
             if constexpr (WS) {
-              if (ws_prev) {
-                float mx = 0.0f;
-#pragma unroll
-                for (int ww = 0; ww < W; ++ww) mx = fmaxf(mx, s_wmx[ww * NR + lane]);
-                wsl = 1.0f - __builtin_amdgcn_sqrtf(mx);
-              }
+              if (ws_prev) wsl = 1.0f - __builtin_amdgcn_sqrtf(__uint_as_float(pm[2 * NR]));
               // ||M_w^{-1} (sum of steps)|| <= sum of ||M_w^{-1} step|| (triangle inequality)
               wsl -= __builtin_amdgcn_sqrtf((d0 * d0 + d1 * d1) * wia2 + d2 * d2 * wib2);
             }
@@ -578,6 +559,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         // iteration.
         float mgx = 0.0f, mgz = 0.0f;
         if (rebuild) {
+          const float cm = fmaxf(fmaxf(s_cm[lane], s_cm[64 + lane]), s_cm[128 + lane]);
           const float tol = 2.44140625e-4f * (wave_max(cm) + fmaxf(skx, skz));
           mgx = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(2.0f * skx + tol)));
           mgz = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(2.0f * skz + tol)));
@@ -598,8 +580,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             for (int d = 0; d < 3; ++d)
 #pragma unroll
               for (int s = 0; s < KS; ++s) {
-                const int robot = 16 * rr + col, kk = 4 * s + grp;
-                bx[rr][d][s] = (robot < n && kk < m) ? sxi[(robot * 3 + d) * m + kk] : 0.0f;
+                // (past m the A operand is zero and the words read hold finite state)
+                bx[rr][d][s] = sxi[(d * m + 4 * s + grp) * NR + 16 * rr + col];
               }
         } else if constexpr (!HBR) {
           // lane (col, grp) takes coefficients 8 (grp & 1) .. + 7 of robot col: hi in the first
@@ -818,7 +800,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
 #pragma unroll
                 for (int d = 0; d < 3; ++d)
 #pragma unroll
-                  for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(Y[rr][d][s], b4[s], gacc[rr][d]);
+                  for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(b4[s], Y[rr][d][s], gacc[rr][d]);
             }
           }
           wave_sync();
@@ -897,353 +879,170 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                 const f4 cr = *cp;
                 *cp = f4{0.0f, 0.0f, 0.0f, 0.0f};     // the accumulator is kept zero between tiles
 #pragma unroll
-                for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(cr[s], b4[s], gacc[rr][d]);
+                for (int s = 0; s < 4; ++s) gacc[rr][d] = mfma4(b4[s], cr[s], gacc[rr][d]);
               }
           }
           wave_sync();
         }
         if constexpr (R == 1) __builtin_amdgcn_s_setprio(2);   // (see the tile phase)
-        // this wave's partial back-projection and bound maxima -> its own LDS region
-        {
-          // Every lane stores, without branches: the rows of phantom robots (past n) fall in the
-          // dead part of the position buffer (it holds 3 x 16R x 16 words), and lanes of the
-          // columns past m (zero products) write distinct spare words after the 3 x 16R rows of m.
-          float* gp = wbuf;
-          const bool cv = col < m;
-          const int spare = NR * 3 * m + (col - m) + (16 - m) * grp;
+        // this wave's partial back-projection -> its own LDS region, as the products leave it (lane (col, grp),
+        // register r: robot col, coefficient grp + 4 r), and its bound maxima
 #pragma unroll
-          for (int rr = 0; rr < R; ++rr)
+        for (int rr = 0; rr < R; ++rr)
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+          for (int d = 0; d < 3; ++d)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int robot = 16 * rr + 4 * grp + r;
-                gp[cv ? (robot * 3 + d) * m + col : spare] = gacc[rr][d][r];
-              }
-          if (grp == 0) {
+            for (int r = 0; r < KS; ++r) wbuf[((d * R + rr) * KS + r) * 64 + lane] = gacc[rr][d][r];
+        if (grp == 0) {
 #pragma unroll
-            for (int rr = 0; rr < R; ++rr) {
-              if (eval_flags & 1) s_vmx[wave * NR + 16 * rr + col] = vm[0][rr];
-              if (eval_flags & 2) s_amx[wave * NR + 16 * rr + col] = vm[1][rr];
-              if constexpr (WS)
-                if (ws_eval) s_wmx[wave * NR + 16 * rr + col] = wsm[rr];
-            }
+          for (int rr = 0; rr < R; ++rr) {
+            uint32_t* pm = s_mx + par * 3 * NR + 16 * rr + col;
+            if (eval_flags & 1) atomicMax(pm, __float_as_uint(vm[0][rr]));
+            if (eval_flags & 2) atomicMax(pm + NR, __float_as_uint(vm[1][rr]));
+            if constexpr (WS)
+              if (ws_eval) atomicMax(pm + 2 * NR, __float_as_uint(wsm[rr]));
           }
         }
         __syncthreads();
-        // Multiplier step (all coefficients) and QP step (free coefficients) of row (robot, axis):
-        // g = F^T rho R summed over the waves, lambda <- lambda - g,
-        // y = xi_bar - xi + lambda - g (+ the first-step correction), and
-        // xi_free += X1 y + X01 mean_robots(y).
-        // With HALVES = 2 a row is owned by two lanes 32 apart in one wave, each taking half of its
-        // free and pinned coefficients; they swap their halves of y and mean(y) for the QP product.
-        // Rows are axis-major, so the robots of one axis sit in aligned groups of 16R lanes.
-        // Every load of the step is issued first, from clamped (always valid) addresses, and a
-        // scheduling barrier keeps the arithmetic after them, so the step waits for LDS once; y is
-        // zero past the free coefficients, so the QP product needs no guard either.
-        if constexpr (QUART) {
-          // Multiplier step and QP step of row (robot, ax), ax = this wave: lane robot + 16 q takes
-          // the free coefficients f = q, q + 4, ... and the pinned ones r = q, q + 4.  Every lane
-          // gathers its row's y and mean(y) from the four quarters with row swaps.
-          const float* gp0 = smem + L.tiles;
-          const int q4 = lane >> 4, rb = lane & 15, ax = wave;
-          const bool on = rb < n;
-          const int row = (on ? rb : 0) * 3 + ax;
-          int qf[FQ], qpn[2];
-          float xv[FQ], lf[FQ], xb[FQ], cr[FQ], gf[FQ][W], lp[2], gn[2][W];
+        if (clear_mx)
+          for (int q = tid; q < 3 * NR; q += nthr) s_mx[(par ^ 1) * 3 * NR + q] = 0u;
+        // Multiplier step and QP step of one axis per wave: lane (rb, q4) holds coefficients q4 + 4 r of robots
+        // rb (and 16 + rb).  g = F^T rho R summed over the waves, lambda <- lambda - g,
+        // y = xi_bar - xi + lambda - g (+ the first-step correction, in xi_bar) on the free coefficients, and
+        // xi_free += X1 y + X01 mean_robots(y).  Every load is issued first and a scheduling barrier keeps the
+        // arithmetic after them; y and its means then reach the lanes of a robot through LDS, in this axis'
+        // partials of wave 0, which no other wave reads.  With two lanes of
+        // half-filled waves walking each row the step was a fifth of an iteration with one robot tile and a
+        // third with two (16 robots x 1024 samples, bf16, 300 iterations: 1.37 -> 1.32 ms; 32 robots x 4096:
+        // 19.7 -> 18.3 ms).
+        for (int ax = wave; ax < 3; ax += W) {
+          float* gp0 = smem + L.tiles + ax * (R * KS * 64);
+          const int q4 = lane >> 4, rb = lane & 15;
+          const int e0 = (ax * m + q4) * NR + rb;
+          float xv[R][KS], lf[R][KS], xb[R][KS], gw[R][KS][W];
 #pragma unroll
-          for (int j = 0; j < FQ; ++j) {
-            const int f = q4 + 4 * j, fc = f < mf ? f : 0;
-            qf[j] = row * m + 3 + fc;
-            xv[j] = sxi[qf[j]];
-            lf[j] = slam[qf[j]];
-            xb[j] = sxb[qf[j]];
-            cr[j] = scorr[row * (mf > 0 ? mf : 1) + fc];
+          for (int rr = 0; rr < R; ++rr)
 #pragma unroll
-            for (int ww = 0; ww < W; ++ww) gf[j][ww] = gp0[ww * L.per_wave + qf[j]];
-          }
+            for (int r = 0; r < KS; ++r) {
+              // (past m: other words, unused)
+              const int e = e0 + 4 * r * NR + 16 * rr;
+              xv[rr][r] = sxi[e];
+              lf[rr][r] = slam[e];
+              xb[rr][r] = sxb[e];
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const int r = q4 + 4 * j, rc = r < kNFix ? r : 0;
-            qpn[j] = row * m + fixed_k(rc);
-            lp[j] = slam[qpn[j]];
-#pragma unroll
-            for (int ww = 0; ww < W; ++ww) gn[j][ww] = gp0[ww * L.per_wave + qpn[j]];
-          }
-          float cmax = s_cmx[row];   // running bound on |coefficient| of the row (pinned values included)
+              for (int ww = 0; ww < W; ++ww) gw[rr][r][ww] = gp0[ww * L.per_wave + (rr * KS + r) * 64 + lane];
+            }
+          float cmax = s_cm[ax * 64 + lane];
           __builtin_amdgcn_sched_barrier(0);
-          auto sumw = [&](const float (&g)[W]) {
-            float s = g[0];
+          float* sy = gp0;                    // y [f][16R robots]
+          float* sym = gp0 + MFX * NR;        // robot means [f], zero past mf
 #pragma unroll
-            for (int ww = 1; ww < W; ++ww) s += g[ww];
-            return s;
-          };
-          // the value of `v` in the four quarters of this lane's row, in quarter order
-          auto quarters = [&](float v, float* out) {
-            const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-            const auto b0 = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
-            const auto b1 = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
-            out[0] = __uint_as_float(b0[0]);
-            out[1] = __uint_as_float(b1[0]);
-            out[2] = __uint_as_float(b0[1]);
-            out[3] = __uint_as_float(b1[1]);
-          };
-          float ln[FQ], yo[FQ], gq[FQ];
+          for (int r = 0; r < KS; ++r) {
+            const int kk = 4 * r + q4, f = kk - 3;
+            const bool fr = f >= 0 && f < mf;
+            float mean = 0.0f;
 #pragma unroll
-          for (int j = 0; j < FQ; ++j) {
-            gq[j] = sumw(gf[j]);
-            ln[j] = lf[j] - gq[j];
-            float yv = xb[j] - xv[j] + ln[j] - gq[j];
-            if (k == 0) yv += cr[j];
-            yo[j] = (on && q4 + 4 * j < mf) ? yv : 0.0f;
+            for (int rr = 0; rr < R; ++rr) {
+              float g = gw[rr][r][0];
+#pragma unroll
+              for (int ww = 1; ww < W; ++ww) g += gw[rr][r][ww];
+              gw[rr][r][0] = g;
+              lf[rr][r] -= g;
+              float yv = xb[rr][r] - xv[rr][r] + lf[rr][r] - g;
+              if constexpr (!LEAN)
+                if (k == 0 && fr) yv += scorr[(ax * mf + f) * NR + rb];
+              const float y = (fr && 16 * rr + rb < n) ? yv : 0.0f;
+              if (f >= 0 && f < MFX) sy[f * NR + 16 * rr + rb] = y;
+              const float s = group_sum<16>(y);
+              mean = rr == 0 ? s : mean + s;
+            }
+            if (rb == 0 && f >= 0 && f < MFX) sym[f] = mean * inv_n;
           }
-          // all free coefficients' y and mean(y): index f = q + 4 j (zero past mf)
-          float ya[4 * FQ], yba[4 * FQ];
+          wave_sync();
+          float ya[R][MFX], yba[QR];
 #pragma unroll
-          for (int j = 0; j < FQ; ++j) {
-            quarters(yo[j], ya + 4 * j);
-            quarters(group_sum<16>(yo[j]) * inv_n, yba + 4 * j);
+          for (int f2 = 0; f2 < MFX; ++f2)
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr) ya[rr][f2] = sy[f2 * NR + 16 * rr + rb];
+#pragma unroll
+          for (int cc = 0; cc < QR / 4; ++cc) {
+            const f4 v = *reinterpret_cast<const f4*>(sym + 4 * cc);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) yba[4 * cc + e] = v[e];
           }
-          float acc[FQ];
+          float dmax[R];
 #pragma unroll
-          for (int j = 0; j < FQ; ++j) {
-            const int f = q4 + 4 * j, fr = f < mf ? f : 0;
-            float a = 0.0f;
+          for (int rr = 0; rr < R; ++rr) dmax[rr] = 0.0f;
 #pragma unroll
-            for (int cc = 0; cc < QC; ++cc) {
-              const f4 x1 = *reinterpret_cast<const f4*>(sX1 + fr * (4 * QC) + 4 * cc);
-              const f4 x01 = *reinterpret_cast<const f4*>(sX1 + (mf + fr) * (4 * QC) + 4 * cc);
+          for (int r = 0; r < KS; ++r) {
+            const int kk = 4 * r + q4, f = kk - 3;
+            const bool fr = f >= 0 && f < mf;
+            float acc[R];
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (4 * cc + e < MFX) {
-                  a = fmaf(x1[e], ya[4 * cc + e], a);
-                  a = fmaf(x01[e], yba[4 * cc + e], a);
+            for (int rr = 0; rr < R; ++rr) acc[rr] = 0.0f;
+            if (4 * r < m - 3) {   // (uniform: some lane group's coefficient is free)
+              const int fc = fr ? f : 0;
+#pragma unroll
+              for (int cc = 0; cc < QR / 4; ++cc) {
+                const f4 x1 = *reinterpret_cast<const f4*>(sX1 + fc * QR + 4 * cc);
+                const f4 x01 = *reinterpret_cast<const f4*>(sX1 + (mf + fc) * QR + 4 * cc);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (4 * cc + e < MFX) {
+#pragma unroll
+                    for (int rr = 0; rr < R; ++rr) {
+                      acc[rr] = fmaf(x1[e], ya[rr][4 * cc + e], acc[rr]);
+                      acc[rr] = fmaf(x01[e], yba[4 * cc + e], acc[rr]);
+                    }
+                  }
+              }
+            }
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr) {
+              const int robot = 16 * rr + rb, e = e0 + 4 * r * NR + 16 * rr;
+              const bool in = robot < n && kk < m;
+              const float dx = acc[rr], xn = xv[rr][r] + dx;
+              if (in && fr) {
+                dmax[rr] = fmaxf(dmax[rr], fabsf(dx));
+                cmax = fmaxf(cmax, fabsf(xn));
+                sxi[e] = xn;
+                if constexpr (MP != 0) put_split(robot, ax, kk, xn);
+              }
+              if (in) slam[e] = lf[rr][r];
+              if (fpr && in) {
+                fpsum = fmaf(gw[rr][r][0], gw[rr][r][0], fpsum);
+                if (fr) fpsum = fmaf(dx, dx, fpsum);
+              }
+            }
+          }
+          s_cm[ax * 64 + lane] = cmax;
+#pragma unroll
+          for (int rr = 0; rr < R; ++rr) {
+            const float dm = grp_max(dmax[rr]);
+            if (q4 == 0) s_dxi[ax * NR + 16 * rr + rb] = dm;
+          }
+          if (k == 0) {
+            // the pinned coefficients move to their boundary values in the first step, and with two robot tiles
+            // xi_bar drops the correction again
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+              for (int r = 0; r < KS; ++r) {
+                const int kk = 4 * r + q4, robot = 16 * rr + rb, e = e0 + 4 * r * NR + 16 * rr;
+                if (robot < n && kk < m) {
+                  const int row = robot * 3 + ax;
+                  if (kk >= 3 && kk < m - 3) {
+                    if constexpr (LEAN) sxb[e] = xi_bar[coef + row * m + kk];
+                  } else {
+                    const float xp = pinned(row, kk < 3 ? kk : kk - (m - kNFix));
+                    if (fpr) fpsum = fmaf(xp - xv[rr][r], xp - xv[rr][r], fpsum);
+                    sxi[e] = xp;
+                    if constexpr (MP != 0) put_split(robot, ax, kk, xp);
+                  }
                 }
-            }
-            acc[j] = a;
-          }
-          float dmax = 0.0f;
-#pragma unroll
-          for (int j = 0; j < FQ; ++j)
-            if (q4 + 4 * j < mf) {
-              dmax = fmaxf(dmax, fabsf(acc[j]));
-              cmax = fmaxf(cmax, fabsf(xv[j] + acc[j]));
-            }
-          {
-            float t[4];
-            quarters(dmax, t);
-            dmax = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
-            quarters(cmax, t);
-            cmax = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
-          }
-          if (fpr && on) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              if (q4 + 4 * j < kNFix) {
-                const float g = sumw(gn[j]);
-                fpsum = fmaf(g, g, fpsum);
-                if (k == 0) {   // the pinned coefficients move to their boundary values in step 0
-                  const float dx = pinned(row, q4 + 4 * j) - sxi[qpn[j]];
-                  fpsum = fmaf(dx, dx, fpsum);
-                }
-              }
-#pragma unroll
-            for (int j = 0; j < FQ; ++j)
-              if (q4 + 4 * j < mf) {
-                fpsum = fmaf(gq[j], gq[j], fpsum);
-                fpsum = fmaf(acc[j], acc[j], fpsum);
               }
           }
-          if (on) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const int r = q4 + 4 * j;
-              if (r < kNFix) {
-                slam[qpn[j]] = lp[j] - sumw(gn[j]);
-                if (k == 0) {
-                  const float xp = pinned(row, r);
-                  sxi[qpn[j]] = xp;
-                  if constexpr (MP != 0) put_split(rb, ax, fixed_k(r), xp);
-                }
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < FQ; ++j) {
-              const int f = q4 + 4 * j;
-              if (f < mf) {
-                const float xn = xv[j] + acc[j];
-                slam[qf[j]] = ln[j];
-                sxi[qf[j]] = xn;
-                if constexpr (MP != 0) put_split(rb, ax, 3 + f, xn);
-              }
-            }
-            if (q4 == 0) {
-              s_dxi[row] = dmax;
-              s_cmx[row] = cmax;   // (the other quarters read it above, in the same wave)
-            }
-          }
-        } else if (wave < TAILW) {
-          const float* gp0 = smem + L.tiles;
-          const int hl = HALVES == 2 ? (lane >> 5) : 0;
-          const int trow = wave * (64 / HALVES) + (HALVES == 2 ? (lane & 31) : lane);
-          const int ax = trow / NR, rb = trow - ax * NR;
-          const bool on = ax < 3 && rb < n;
-          const int row = on ? rb * 3 + ax : 0;
-          constexpr int PF = kNFix / HALVES;                  // pinned coefficients per lane
-          constexpr int QD = FHP > 4 ? 1 : 2;                 // QP rows loaded ahead of their use
-          int qq[PF];
-          float lp[PF], gr[PF + FH][W], xv[FH], lf[FH], xb[FH], cr[FH];
-          int qx[FH];
-          f4 qa[QD][FHP / 4], qb[QD][FHP / 4];
-          auto qp_row = [&](int f2, f4 (&a1)[FHP / 4], f4 (&a2)[FHP / 4]) {
-            const int rc = max(0, min(f2, mf - 1));
-#pragma unroll
-            for (int cc = 0; cc < FHP / 4; ++cc) {
-              a1[cc] = *reinterpret_cast<const f4*>(sX1 + ((0 * HALVES + hl) * mf + rc) * FHP + 4 * cc);
-              a2[cc] = *reinterpret_cast<const f4*>(sX1 + ((1 * HALVES + hl) * mf + rc) * FHP + 4 * cc);
-            }
-          };
-#pragma unroll
-          for (int j = 0; j < PF; ++j) {
-            qq[j] = row * m + fixed_k(hl * PF + j);
-            lp[j] = slam[qq[j]];
-#pragma unroll
-            for (int ww = 0; ww < W; ++ww) gr[j][ww] = gp0[ww * L.per_wave + qq[j]];
-          }
-#pragma unroll
-          for (int j = 0; j < FH; ++j) {
-            const int fc = max(0, min(hl * FH + j, mf - 1));
-            const int q = row * m + 3 + fc;
-            qx[j] = q;
-            xv[j] = sxi[q];
-            lf[j] = slam[q];
-            xb[j] = sxb[q];
-            cr[j] = LEAN ? 0.0f : scorr[row * (mf > 0 ? mf : 1) + fc];
-#pragma unroll
-            for (int ww = 0; ww < W; ++ww) gr[PF + j][ww] = gp0[ww * L.per_wave + q];
-          }
-          float cmax = s_cmx[row];   // running bound on |coefficient| of the row (pinned values included)
-#pragma unroll
-          for (int f2 = 0; f2 < QD; ++f2) qp_row(f2, qa[f2], qb[f2]);
-          __builtin_amdgcn_sched_barrier(0);
-          auto gsum = [&](int j) {
-            float g = gr[j][0];
-#pragma unroll
-            for (int ww = 1; ww < W; ++ww) g += gr[j][ww];
-            return g;
-          };
-          // pinned coefficients: multiplier step (their boundary values are set in step 0 below)
-          float nl[PF];
-#pragma unroll
-          for (int j = 0; j < PF; ++j) nl[j] = lp[j] - gsum(j);
-          // free coefficients f = hl * FH + j
-          float yo[FH], ln[FH];
-#pragma unroll
-          for (int j = 0; j < FH; ++j) {
-            const int f = hl * FH + j;
-            const float g = gsum(PF + j);
-            ln[j] = lf[j] - g;
-            float yv = xb[j] - xv[j] + ln[j] - g;
-            if (k == 0) {
-              if constexpr (LEAN) {
-                if (on && f < mf) sxb[qx[j]] = xi_bar[coef + qx[j]];   // drop the correction again
-              } else {
-                yv += cr[j];
-              }
-            }
-            yo[j] = (on && f < mf) ? yv : 0.0f;
-          }
-          float ybo[FH];
-#pragma unroll
-          for (int j = 0; j < FH; ++j) ybo[j] = group_sum<NR>(yo[j]) * inv_n;
-          // all free coefficients' y and mean(y), in order (zero past mf)
-          float ya[HALVES * FH], yba[HALVES * FH];
-#pragma unroll
-          for (int j = 0; j < FH; ++j) {
-            if constexpr (HALVES == 2) {
-              const auto sy = __builtin_amdgcn_permlane32_swap(__float_as_uint(yo[j]), __float_as_uint(yo[j]), false, false);
-              const auto sb2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(ybo[j]), __float_as_uint(ybo[j]), false, false);
-              ya[j] = __uint_as_float(sy[0]);        // half 0
-              ya[FH + j] = __uint_as_float(sy[1]);   // half 1
-              yba[j] = __uint_as_float(sb2[0]);
-              yba[FH + j] = __uint_as_float(sb2[1]);
-            } else {
-              ya[j] = yo[j];
-              yba[j] = ybo[j];
-            }
-          }
-          // own outputs: acc[j] = sum_f2 X1[f][f2] y[f2] + X01[f][f2] mean(y)[f2], f2 in order
-          float acc[FHP];
-#pragma unroll
-          for (int j = 0; j < FHP; ++j) acc[j] = 0.0f;
-          // (rows QD ahead are loaded as each row is used; the barriers keep that order)
-#pragma unroll
-          for (int f2 = 0; f2 < MFX; ++f2) {
-            const int sl = f2 % QD;
-#pragma unroll
-            for (int j = 0; j < FHP; ++j) {
-              acc[j] = fmaf(qa[sl][j / 4][j % 4], ya[f2], acc[j]);
-              acc[j] = fmaf(qb[sl][j / 4][j % 4], yba[f2], acc[j]);
-            }
-            if (f2 + QD < MFX) qp_row(f2 + QD, qa[sl], qb[sl]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          float dmax = 0.0f;
-#pragma unroll
-          for (int j = 0; j < FH; ++j)
-            if (hl * FH + j < mf) {
-              dmax = fmaxf(dmax, fabsf(acc[j]));
-              cmax = fmaxf(cmax, fabsf(xv[j] + acc[j]));
-            }
-          if constexpr (HALVES == 2) {
-            const auto sd = __builtin_amdgcn_permlane32_swap(__float_as_uint(dmax), __float_as_uint(dmax), false, false);
-            dmax = fmaxf(__uint_as_float(sd[0]), __uint_as_float(sd[1]));
-            const auto sc = __builtin_amdgcn_permlane32_swap(__float_as_uint(cmax), __float_as_uint(cmax), false, false);
-            cmax = fmaxf(__uint_as_float(sc[0]), __uint_as_float(sc[1]));
-          }
-          if (fpr && on) {
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-              const float g = gsum(j);
-              fpsum = fmaf(g, g, fpsum);
-              if (k == 0) {   // the pinned coefficients move to their boundary values in step 0
-                const float dx = pinned(row, hl * PF + j) - sxi[qq[j]];
-                fpsum = fmaf(dx, dx, fpsum);
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < FH; ++j)
-              if (hl * FH + j < mf) {
-                const float g = gsum(PF + j);
-                fpsum = fmaf(g, g, fpsum);
-                fpsum = fmaf(acc[j], acc[j], fpsum);
-              }
-          }
-          if (on) {
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-              slam[qq[j]] = nl[j];
-              if (k == 0) {
-                const float xp = pinned(row, hl * PF + j);
-                sxi[qq[j]] = xp;
-                if constexpr (MP != 0) put_split(rb, ax, fixed_k(hl * PF + j), xp);
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < FH; ++j) {
-              const int f = hl * FH + j;
-              if (f < mf) {
-                const float xn = xv[j] + acc[j];
-                slam[row * m + 3 + f] = ln[j];
-                sxi[row * m + 3 + f] = xn;
-                if constexpr (MP != 0) put_split(rb, ax, 3 + f, xn);
-              }
-            }
-            if (hl == 0) {
-              s_dxi[row] = dmax;
-              s_cmx[row] = cmax;   // (the other half read it above, in the same wave)
-            }
-          }
+          if constexpr (W >= 3) break;   // (one axis per wave)
         }
         __syncthreads();
       }
@@ -1264,7 +1063,11 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           // One basis product of a tile for the iterate in `src` (previous or new).  The B operands
           // are formed per product (this runs once per solve), so that only one iterate's
           // products are live at a time.
-          auto prod = [&](const float* src, int tau, int b, f4 (&Y)[R][3]) {
+          // (prev: the previous iterate, in LDS or, with two robot tiles, in xi_out)
+          auto prod = [&](bool prev, int tau, int b, f4 (&Y)[R][3]) {
+            const float* src = prev ? (LEAN ? xi_out + coef : sxprev) : sxi;
+            const bool glob = LEAN && prev;
+            const int sr = glob ? 3 * m : 1, sd = glob ? m : m * NR, sk = glob ? 1 : NR;
             if constexpr (MP == 0) {
               const float4 av = a32c[((tau * 3 + b) * 2) * 64 + lane];
               const float a1[4] = {av.x, av.y, av.z, av.w};
@@ -1276,7 +1079,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
 #pragma unroll
                   for (int s = 0; s < KS; ++s) {
                     const int robot = 16 * rr + col, kk = 4 * s + grp;
-                    const float v = (robot < n && kk < m) ? src[(robot * 3 + d) * m + kk] : 0.0f;
+                    const float v = (robot < n && kk < m) ? src[robot * sr + d * sd + kk * sk] : 0.0f;
                     acc = mfma4(a1[s], v, acc);
                   }
                   Y[rr][d] = acc;
@@ -1291,7 +1094,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
                   V h1, h2;
-                  split_xi<MP>(src, 16 * rr + col, n, m, d, grp, h1, h2);
+                  const int robot = 16 * rr + col;
+                  split_xi<MP>(src + (robot < n ? robot * sr + d * sd : 0), sk, robot < n, m, grp, h1, h2);
                   f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
                   acc = mfma16(A1, h1, acc);
                   acc = mfma16(A2, h2, acc);
@@ -1310,8 +1114,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               if (b > 0 && !(b == 1 ? c.vel_on : c.acc_on)) continue;
               const float lim = b == 1 ? vmax : amax;
               f4 Y[R][3];
-              if constexpr (LEAN) prod(xi_out + coef, tau, b, Y);
-              else prod(sxprev, tau, b, Y);
+              prod(true, tau, b, Y);
               if (b == 0) {
 #pragma unroll
                 for (int rr = 0; rr < R; ++rr)
@@ -1333,7 +1136,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                   }
               }
               f4 Yn[R][3];
-              prod(sxi, tau, b, Yn);
+              prod(false, tau, b, Yn);
               if (b == 0) {
 #pragma unroll
                 for (int rr = 0; rr < R; ++rr)
@@ -1425,8 +1228,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         __syncthreads();
       }
       for (int q = tid; q < nDm; q += nthr) {
-        xi_out[coef + q] = sxi[q];
-        if (lam_out) lam_out[coef + q] = slam[q];
+        const int e = state_at(q);
+        xi_out[coef + q] = sxi[e];
+        if (lam_out) lam_out[coef + q] = slam[e];
       }
       // convergence bits (the status pass adds the finiteness of the outputs)
       if (status_out && tid == 0) status_out[sidx] = in_flag < 0 ? in_flag : sample_status<float>(false, false, rmax, iters_s);
@@ -1483,13 +1287,6 @@ fast_batched_kernel(FastArgs A, int* __restrict__ queue) {
   }
 }
 
-// Resets the queue heads of a launch sequence (a kernel node rather than a memset, so the
-// sequence can be captured in a graph).
-__global__ void reset_queue_kernel(int* queue, int n) {
-  if (threadIdx.x == 0 && blockIdx.x == 0)
-    for (int i = 0; i < n; ++i) queue[i] = 0;
-}
-
 // Kernel instances: R robot tiles of 16, KS k-steps of 4 coefficients, W waves per workgroup.
 // Target waves per SIMD (the register budget): 3 with one robot tile (168 VGPRs; three waves per
 // sample then keep four samples per CU resident); with two robot tiles 2 for three or four waves
@@ -1532,15 +1329,14 @@ hipError_t launch_segments_instance(const FastPlan& p, const LaunchArgs& a, cons
 }
 
 // Single-shape batch, at the waves per sample a small batch runs with (4, with a workspace 3).
-template <int MP, int WS>
+template <int MP, int WS, int R>
 hipError_t launch_segments_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
   constexpr int W = WS ? 3 : 4;
-  switch (p.R * 10 + p.KS) {
-    case 12: return launch_segments_instance<1, 2, W, MP, WS>(p, a, tab32, a16);
-    case 13: return launch_segments_instance<1, 3, W, MP, WS>(p, a, tab32, a16);
-    case 14: return launch_segments_instance<1, 4, W, MP, WS>(p, a, tab32, a16);
-    case 23: return launch_segments_instance<2, 3, W, MP, WS>(p, a, tab32, a16);
-    case 24: return launch_segments_instance<2, 4, W, MP, WS>(p, a, tab32, a16);
+  if constexpr (R == 1)
+    if (p.KS == 2) return launch_segments_instance<R, 2, W, MP, WS>(p, a, tab32, a16);
+  switch (p.KS) {
+    case 3: return launch_segments_instance<R, 3, W, MP, WS>(p, a, tab32, a16);
+    case 4: return launch_segments_instance<R, 4, W, MP, WS>(p, a, tab32, a16);
     default: break;
   }
   fast_set_error("no kernel instance for this shape");
@@ -1575,78 +1371,50 @@ hipError_t launch_class_w(const FastClass& C, const FastArgs& f, int grid, int W
 }
 
 // Single-shape launch of the instance for (R, KS, W) of this precision and workspace flag.
-template <int MP, int WS>
+template <int MP, int WS, int R, int KS>
+hipError_t launch_single_w(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16, int W) {
+  switch (W) {
+    case 2: return launch_instance<R, KS, 2, MP, WS>(p, a, tab32, a16);
+    case 3: return launch_instance<R, KS, 3, MP, WS>(p, a, tab32, a16);
+    case 4:   // (with the workspace rows: 2 or 3 waves per workgroup)
+      if constexpr (WS == 0) return launch_instance<R, KS, 4, MP, WS>(p, a, tab32, a16);
+      break;
+    default: break;
+  }
+  fast_set_error("no kernel instance for this shape");
+  return hipErrorNotSupported;
+}
+template <int MP, int WS, int R>
 hipError_t launch_single_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16, int W) {
-  const int key = p.R * 100 + p.KS * 10 + W;
-  if constexpr (WS == 0) {
-    switch (key) {
-      case 122: return launch_instance<1, 2, 2, MP, 0>(p, a, tab32, a16);
-      case 123: return launch_instance<1, 2, 3, MP, 0>(p, a, tab32, a16);
-      case 124: return launch_instance<1, 2, 4, MP, 0>(p, a, tab32, a16);
-      case 132: return launch_instance<1, 3, 2, MP, 0>(p, a, tab32, a16);
-      case 133: return launch_instance<1, 3, 3, MP, 0>(p, a, tab32, a16);
-      case 134: return launch_instance<1, 3, 4, MP, 0>(p, a, tab32, a16);
-      case 142: return launch_instance<1, 4, 2, MP, 0>(p, a, tab32, a16);
-      case 143: return launch_instance<1, 4, 3, MP, 0>(p, a, tab32, a16);
-      case 144: return launch_instance<1, 4, 4, MP, 0>(p, a, tab32, a16);
-      case 232: return launch_instance<2, 3, 2, MP, 0>(p, a, tab32, a16);
-      case 233: return launch_instance<2, 3, 3, MP, 0>(p, a, tab32, a16);
-      case 234: return launch_instance<2, 3, 4, MP, 0>(p, a, tab32, a16);
-      case 242: return launch_instance<2, 4, 2, MP, 0>(p, a, tab32, a16);
-      case 243: return launch_instance<2, 4, 3, MP, 0>(p, a, tab32, a16);
-      case 244: return launch_instance<2, 4, 4, MP, 0>(p, a, tab32, a16);
-      default: break;
-    }
-  } else {
-    // with the workspace rows: 2 or 3 waves per workgroup
-    switch (key) {
-      case 122: return launch_instance<1, 2, 2, MP, 1>(p, a, tab32, a16);
-      case 123: return launch_instance<1, 2, 3, MP, 1>(p, a, tab32, a16);
-      case 132: return launch_instance<1, 3, 2, MP, 1>(p, a, tab32, a16);
-      case 133: return launch_instance<1, 3, 3, MP, 1>(p, a, tab32, a16);
-      case 142: return launch_instance<1, 4, 2, MP, 1>(p, a, tab32, a16);
-      case 143: return launch_instance<1, 4, 3, MP, 1>(p, a, tab32, a16);
-      case 232: return launch_instance<2, 3, 2, MP, 1>(p, a, tab32, a16);
-      case 233: return launch_instance<2, 3, 3, MP, 1>(p, a, tab32, a16);
-      case 242: return launch_instance<2, 4, 2, MP, 1>(p, a, tab32, a16);
-      case 243: return launch_instance<2, 4, 3, MP, 1>(p, a, tab32, a16);
-      default: break;
-    }
+  if constexpr (R == 1)
+    if (p.KS == 2) return launch_single_w<MP, WS, R, 2>(p, a, tab32, a16, W);
+  switch (p.KS) {
+    case 3: return launch_single_w<MP, WS, R, 3>(p, a, tab32, a16, W);
+    case 4: return launch_single_w<MP, WS, R, 4>(p, a, tab32, a16, W);
+    default: break;
   }
   fast_set_error("no kernel instance for this shape");
   return hipErrorNotSupported;
 }
 
-// Persistent launch sequence (one kernel per robot-tile class) of this precision and workspace flag:
-// the queue heads are reset, then each class selected by cls_mask runs with its own waves per
-// workgroup W[c] and workgroup count grid[c] (0 = the class's default).
-template <int MP, int WS>
-hipError_t launch_batched_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16,
-                             const int* grid, const int* W, int cls_mask) {
-  hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, a.stream, p.d_queue, p.n_cls);
-  for (int ci = 0; ci < p.n_cls; ++ci) {
-    if (!(cls_mask & (1 << ci))) continue;
-    const FastClass& C = p.cls[ci];
-    FastArgs f = make_fast_args(a, tab32, a16);
-    f.items = p.d_items_sorted + C.offset;
-    f.n_items = C.n_items;
-    const int g = std::max(1, std::min(C.n_items, grid[ci] > 0 ? grid[ci] : C.grid));
-    int* q = p.d_queue + ci;
-    hipError_t e;
-    switch (C.R * 10 + p.KS) {
-      case 12: e = launch_class_w<1, 2, MP, WS>(C, f, g, W[ci], q, a.stream); break;
-      case 13: e = launch_class_w<1, 3, MP, WS>(C, f, g, W[ci], q, a.stream); break;
-      case 14: e = launch_class_w<1, 4, MP, WS>(C, f, g, W[ci], q, a.stream); break;
-      case 22: e = launch_class_w<2, 2, MP, WS>(C, f, g, W[ci], q, a.stream); break;
-      case 23: e = launch_class_w<2, 3, MP, WS>(C, f, g, W[ci], q, a.stream); break;
-      case 24: e = launch_class_w<2, 4, MP, WS>(C, f, g, W[ci], q, a.stream); break;
-      default:
-        fast_set_error("no persistent kernel instance for this shape");
-        return hipErrorNotSupported;
-    }
-    if (e != hipSuccess) return e;
+// Class ci (of R robot tiles) of a persistent launch sequence with W waves per workgroup; grid > 0: workgroups
+// (at most the class's work items), 0: the class's default.
+template <int MP, int WS, int R>
+hipError_t launch_batched_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16, int ci,
+                             int grid, int W) {
+  const FastClass& C = p.cls[ci];
+  FastArgs f = make_fast_args(a, tab32, a16);
+  f.items = p.d_items_sorted + C.offset;
+  f.n_items = C.n_items;
+  const int g = std::max(1, std::min(C.n_items, grid > 0 ? grid : C.grid));
+  switch (p.KS) {
+    case 2: return launch_class_w<R, 2, MP, WS>(C, f, g, W, p.d_queue + ci, a.stream);
+    case 3: return launch_class_w<R, 3, MP, WS>(C, f, g, W, p.d_queue + ci, a.stream);
+    case 4: return launch_class_w<R, 4, MP, WS>(C, f, g, W, p.d_queue + ci, a.stream);
+    default: break;
   }
-  return hipSuccess;
+  fast_set_error("no persistent kernel instance for this shape");
+  return hipErrorNotSupported;
 }
 
 }  // namespace
