@@ -153,9 +153,9 @@ __host__ __device__ inline FastLds fast_lds_plan(const DevCfg& c, int R, int KS,
   p.corr = o; o += R == 1 ? 3 * c.mf * nr : 0;   // first-step correction [axis][f][16R robots]
   p.pairs = o; o += R == 2 ? 0 : Npmax;  // (two robot tiles: in the pair-list regions)
   p.mx = o; o += 2 * 3 * nr;               // [evaluation parity][v, a, workspace][robot]: largest squares
-  p.dxi = o; o += 3 * nr;                  // per (axis, robot): max |change| of a free coefficient
   p.cm = o; o += 3 * 64;                   // per axis and tail lane: max |coefficient| over the iterates
   o = (o + 3) & ~3;
+  p.dxi = o; o += 4 * nr;                  // [robot][axis (, pad)]: max |change| of a free coefficient
   p.qp = o; o += 2 * c.mf * qp_row(KS);    // X1, X01: rows of free coefficients, zero-padded
   o = (o + 3) & ~3;
   p.hb = o; o += MP ? 3 * nr * hb_row(R) : 0; // 16-bit S1 B operands: [axis][robot][hi x16, lo x16 (, pad)]
@@ -410,7 +410,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         sxi[e] = xi0 ? xi0[coef + q] : x;
         slam[e] = lam0 ? lam0[coef + q] : 0.0f;
       }
-      for (int q = tid; q < 3 * NR; q += nthr) s_dxi[q] = 0.0f;
+      for (int q = tid; q < 4 * NR; q += nthr) s_dxi[q] = 0.0f;
       for (int q = tid; q < 2 * 3 * NR; q += nthr) s_mx[q] = 0u;
       for (int q = lane; q < 3 * NR * 16; q += 64) Ct[q] = 0.0f;
       // a sample the input check flagged (non-finite input) is not iterated; the status pass then
@@ -503,13 +503,15 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         const int par = k & 1;
         const bool clear_mx = (prev_eval | ws_prev) != 0;   // the other buffer holds the last evaluation
         int eval_flags = 3;
+        bool rebuild = true, ws_eval = false;
         {
-          float dn = 0.0f;
-          if (lane < n) {
-            // margins to the bounds measured by the previous iteration if it evaluated them
-            // (every wave computes the same values).  The hardware square root (1 ulp) serves: the
-            // test below keeps a 1e-4 relative slack, far above its error.
-            const uint32_t* pm = s_mx + (par ^ 1) * 3 * NR + lane;
+          // margins to the bounds measured by the previous iteration if it evaluated them
+          // (every wave computes the same values).  The hardware square root (1 ulp) serves: the
+          // test below keeps a 1e-4 relative slack, far above its error.  (Lanes past the swarm carry
+          // other words and are left out of the tests.)
+          const f4 dx = *reinterpret_cast<const f4*>(s_dxi + 4 * (lane & (NR - 1)));
+          if ((prev_eval | ws_prev) != 0) {
+            const uint32_t* pm = s_mx + (par ^ 1) * 3 * NR + (lane & (NR - 1));
             if (prev_eval & 1) {
               mv = vmax - __builtin_amdgcn_sqrtf(__uint_as_float(pm[0]));
               dv = 0.0f;
@@ -518,38 +520,41 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               ma = amax - __builtin_amdgcn_sqrtf(__uint_as_float(pm[NR]));
               da = 0.0f;
             }
-            const float d0 = s_dxi[lane], d1 = s_dxi[NR + lane], d2 = s_dxi[2 * NR + lane];
-            dn = __builtin_amdgcn_sqrtf(d0 * d0 + d1 * d1 + d2 * d2);
-            px_ += d0;
-            py_ += d1;
-            pz_ += d2;
-            if constexpr (WS) {
+            if constexpr (WS)
               if (ws_prev) wsl = 1.0f - __builtin_amdgcn_sqrtf(__uint_as_float(pm[2 * NR]));
-              // ||M_w^{-1} (sum of steps)|| <= sum of ||M_w^{-1} step|| (triangle inequality)
-              wsl -= __builtin_amdgcn_sqrtf((d0 * d0 + d1 * d1) * wia2 + d2 * d2 * wib2);
-            }
           }
+          const float dn = __builtin_amdgcn_sqrtf(dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]);
+          px_ += dx[0];
+          py_ += dx[1];
+          pz_ += dx[2];
           dv += Lv * dn;
           da += La * dn;
-          const bool fv = c.vel_on && lane < n && dv >= mv - 1e-4f * vmax;
-          const bool fa = c.acc_on && lane < n && da >= ma - 1e-4f * amax;
-          if (k >= 2) eval_flags = (ballot(fv) != 0 ? 1 : 0) | (ballot(fa) != 0 ? 2 : 0);
+          // ||M_w^{-1} (sum of steps)|| <= sum of ||M_w^{-1} step|| (triangle inequality)
+          if constexpr (WS) wsl -= __builtin_amdgcn_sqrtf((dx[0] * dx[0] + dx[1] * dx[1]) * wia2 + dx[2] * dx[2] * wib2);
+          const bool fv = c.vel_on && dv >= mv - 1e-4f * vmax;
+          const bool fa = c.acc_on && da >= ma - 1e-4f * amax;
+          // Workspace rows: a position moves per step by at most the largest coefficient change
+          // per axis, so while max ||M_w^{-1} (p - p_w)|| at the last evaluation plus the summed
+          // scaled drift stays below 1 (1e-4 slack) every workspace residual is exactly zero and the
+          // rows are skipped.
+          const bool fw = WS && c.ws_on && wsl <= 1e-4f;
+          // Rebuild the pair lists when some robot may have moved by more than the margin they were
+          // built with (and in iterations 0 and 1, where the pinned coefficients jump).
+          const bool fr = px_ > skx || py_ > skx || pz_ > skz;
+          if (k >= 2) {
+            eval_flags = 0;
+            rebuild = false;
+            if (ballot(lane < n && (fv || fa || fw || fr)) != 0) {   // (most iterations evaluate nothing)
+              eval_flags = (ballot(lane < n && fv) != 0 ? 1 : 0) | (ballot(lane < n && fa) != 0 ? 2 : 0);
+              rebuild = ballot(lane < n && fr) != 0;
+              if constexpr (WS) ws_eval = ballot(lane < n && fw) != 0;
+            }
+          } else if constexpr (WS) {
+            ws_eval = c.ws_on;
+          }
+          if constexpr (WS) ws_prev = ws_eval;
         }
         prev_eval = eval_flags;
-        // Workspace rows: a position moves per step by at most the largest coefficient change
-        // per axis, so while max ||M_w^{-1} (p - p_w)|| at the last evaluation plus the summed
-        // scaled drift stays below 1 (1e-4 slack) every workspace residual is exactly zero and the
-        // rows are skipped.
-        bool ws_eval = false;
-        if constexpr (WS) {
-          if (c.ws_on) {
-            ws_eval = k < 2 || ballot(lane < n && wsl <= 1e-4f) != 0;
-            ws_prev = ws_eval;
-          }
-        }
-        // Rebuild the pair lists when some robot may have moved by more than the margin they were
-        // built with (and in iterations 0 and 1, where the pinned coefficients jump).
-        const bool rebuild = k < 2 || ballot(lane < n && (px_ > skx || py_ > skx || pz_ > skz)) != 0;
         if (rebuild) px_ = py_ = pz_ = 0.0f;
         // Margins of the broad phase: twice the drift margin per axis, plus the rounding of the
         // positions.  A computed position is a rounded convex combination of its coefficients, off by
@@ -920,6 +925,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           const int q4 = lane >> 4, rb = lane & 15;
           const int e0 = (ax * m + q4) * NR + rb;
           float xv[R][KS], lf[R][KS], xb[R][KS], gw[R][KS][W];
+          constexpr bool EARLY = R == 1;   // (two robot tiles: no registers left to load the matrices ahead)
+          f4 x1[EARLY ? KS - 1 : 1][QR / 4], x01[EARLY ? KS - 1 : 1][QR / 4];
 #pragma unroll
           for (int rr = 0; rr < R; ++rr)
 #pragma unroll
@@ -933,14 +940,23 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               for (int ww = 0; ww < W; ++ww) gw[rr][r][ww] = gp0[ww * L.per_wave + (rr * KS + r) * 64 + lane];
             }
           float cmax = s_cm[ax * 64 + lane];
+          auto qp_rows = [&](int r, f4 (&a)[QR / 4], f4 (&b)[QR / 4]) {   // (rows of a free coefficient, else any)
+            const int fc = max(0, min(4 * r + q4 - 3, mf - 1));
+#pragma unroll
+            for (int cc = 0; cc < QR / 4; ++cc) {
+              a[cc] = *reinterpret_cast<const f4*>(sX1 + fc * QR + 4 * cc);
+              b[cc] = *reinterpret_cast<const f4*>(sX1 + (mf + fc) * QR + 4 * cc);
+            }
+          };
+#pragma unroll
+          for (int r = 0; r < (EARLY ? KS - 1 : 0); ++r) qp_rows(r, x1[r], x01[r]);
           __builtin_amdgcn_sched_barrier(0);
-          float* sy = gp0;                    // y [f][16R robots]
-          float* sym = gp0 + MFX * NR;        // robot means [f], zero past mf
+          float* sy = gp0;                    // y [coefficient][16R robots], zero on the pinned ones
+          float* sym = gp0 + L.per_wave;      // robot means [coefficient][16]
+          float sum[KS];
 #pragma unroll
           for (int r = 0; r < KS; ++r) {
-            const int kk = 4 * r + q4, f = kk - 3;
-            const bool fr = f >= 0 && f < mf;
-            float mean = 0.0f;
+            const int kk = 4 * r + q4;
 #pragma unroll
             for (int rr = 0; rr < R; ++rr) {
               float g = gw[rr][r][0];
@@ -950,76 +966,82 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               lf[rr][r] -= g;
               float yv = xb[rr][r] - xv[rr][r] + lf[rr][r] - g;
               if constexpr (!LEAN)
-                if (k == 0 && fr) yv += scorr[(ax * mf + f) * NR + rb];
-              const float y = (fr && 16 * rr + rb < n) ? yv : 0.0f;
-              if (f >= 0 && f < MFX) sy[f * NR + 16 * rr + rb] = y;
-              const float s = group_sum<16>(y);
-              mean = rr == 0 ? s : mean + s;
+                if (k == 0 && kk >= 3 && kk < m - 3) yv += scorr[(ax * mf + kk - 3) * NR + rb];
+              const float y = (kk >= 3 && kk < m - 3 && 16 * rr + rb < n) ? yv : 0.0f;
+              sy[kk * NR + 16 * rr + rb] = y;
+              const float t = group_sum<16>(y);
+              sum[r] = rr == 0 ? t : sum[r] + t;
             }
-            if (rb == 0 && f >= 0 && f < MFX) sym[f] = mean * inv_n;
           }
+#pragma unroll
+          for (int r = 0; r < KS; ++r) sym[(4 * r + q4) * 16 + rb] = sum[r] * inv_n;
           wave_sync();
-          float ya[R][MFX], yba[QR];
+          float ya[R][MFX], yba[MFX];
 #pragma unroll
-          for (int f2 = 0; f2 < MFX; ++f2)
+          for (int f2 = 0; f2 < MFX; ++f2) {
 #pragma unroll
-            for (int rr = 0; rr < R; ++rr) ya[rr][f2] = sy[f2 * NR + 16 * rr + rb];
-#pragma unroll
-          for (int cc = 0; cc < QR / 4; ++cc) {
-            const f4 v = *reinterpret_cast<const f4*>(sym + 4 * cc);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) yba[4 * cc + e] = v[e];
+            for (int rr = 0; rr < R; ++rr) ya[rr][f2] = sy[(f2 + 3) * NR + 16 * rr + rb];
+            yba[f2] = sym[(f2 + 3) * 16];
           }
+          float acc[R][KS];
+          auto qp_step = [&](int r, const f4 (&a)[QR / 4], const f4 (&b)[QR / 4]) {
+#pragma unroll
+            for (int f2 = 0; f2 < MFX; ++f2)
+#pragma unroll
+              for (int rr = 0; rr < R; ++rr) {
+                acc[rr][r] = fmaf(a[f2 / 4][f2 % 4], ya[rr][f2], acc[rr][r]);
+                acc[rr][r] = fmaf(b[f2 / 4][f2 % 4], yba[f2], acc[rr][r]);
+              }
+          };
           float dmax[R];
+          // new coefficients 4 r + q4 (phantom robots store their zeros)
+          auto finish = [&](int r) {
+            const int kk = 4 * r + q4;
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr) {
+              const bool upd = kk >= 3 && kk < m - 3 && 16 * rr + rb < n;
+              if (fpr && 16 * rr + rb < n && kk < m) {
+                fpsum = fmaf(gw[rr][r][0], gw[rr][r][0], fpsum);
+                if (upd) fpsum = fmaf(acc[rr][r], acc[rr][r], fpsum);
+              }
+              dmax[rr] = fmaxf(dmax[rr], upd ? fabsf(acc[rr][r]) : 0.0f);
+              xb[rr][r] = upd ? xv[rr][r] + acc[rr][r] : xv[rr][r];
+              cmax = fmaxf(cmax, kk < m ? fabsf(xb[rr][r]) : 0.0f);
+            }
+            if (kk < m) {
+#pragma unroll
+              for (int rr = 0; rr < R; ++rr) {
+                const int e = e0 + 4 * r * NR + 16 * rr;
+                sxi[e] = xb[rr][r];
+                slam[e] = lf[rr][r];
+                if constexpr (MP != 0) put_split(16 * rr + rb, ax, kk, xb[rr][r]);
+              }
+            }
+          };
 #pragma unroll
           for (int rr = 0; rr < R; ++rr) dmax[rr] = 0.0f;
 #pragma unroll
-          for (int r = 0; r < KS; ++r) {
-            const int kk = 4 * r + q4, f = kk - 3;
-            const bool fr = f >= 0 && f < mf;
-            float acc[R];
+          for (int r = 0; r < KS; ++r)
 #pragma unroll
-            for (int rr = 0; rr < R; ++rr) acc[rr] = 0.0f;
-            if (4 * r < m - 3) {   // (uniform: some lane group's coefficient is free)
-              const int fc = fr ? f : 0;
+            for (int rr = 0; rr < R; ++rr) acc[rr][r] = 0.0f;
 #pragma unroll
-              for (int cc = 0; cc < QR / 4; ++cc) {
-                const f4 x1 = *reinterpret_cast<const f4*>(sX1 + fc * QR + 4 * cc);
-                const f4 x01 = *reinterpret_cast<const f4*>(sX1 + (mf + fc) * QR + 4 * cc);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  if (4 * cc + e < MFX) {
-#pragma unroll
-                    for (int rr = 0; rr < R; ++rr) {
-                      acc[rr] = fmaf(x1[e], ya[rr][4 * cc + e], acc[rr]);
-                      acc[rr] = fmaf(x01[e], yba[4 * cc + e], acc[rr]);
-                    }
-                  }
-              }
-            }
-#pragma unroll
-            for (int rr = 0; rr < R; ++rr) {
-              const int robot = 16 * rr + rb, e = e0 + 4 * r * NR + 16 * rr;
-              const bool in = robot < n && kk < m;
-              const float dx = acc[rr], xn = xv[rr][r] + dx;
-              if (in && fr) {
-                dmax[rr] = fmaxf(dmax[rr], fabsf(dx));
-                cmax = fmaxf(cmax, fabsf(xn));
-                sxi[e] = xn;
-                if constexpr (MP != 0) put_split(robot, ax, kk, xn);
-              }
-              if (in) slam[e] = lf[rr][r];
-              if (fpr && in) {
-                fpsum = fmaf(gw[rr][r][0], gw[rr][r][0], fpsum);
-                if (fr) fpsum = fmaf(dx, dx, fpsum);
-              }
-            }
+          for (int r = 0; r < KS - 1; ++r) {
+            if constexpr (!EARLY) qp_rows(r, x1[0], x01[0]);
+            qp_step(r, x1[EARLY ? r : 0], x01[EARLY ? r : 0]);
+            if constexpr (!EARLY) finish(r);
           }
+          if (m == 4 * KS) {   // (else the last coefficients of every lane are pinned)
+            f4 xl[QR / 4], xl01[QR / 4];
+            qp_rows(KS - 1, xl, xl01);
+            qp_step(KS - 1, xl, xl01);
+          }
+#pragma unroll
+          for (int r = EARLY ? 0 : KS - 1; r < KS; ++r) finish(r);
           s_cm[ax * 64 + lane] = cmax;
 #pragma unroll
           for (int rr = 0; rr < R; ++rr) {
             const float dm = grp_max(dmax[rr]);
-            if (q4 == 0) s_dxi[ax * NR + 16 * rr + rb] = dm;
+            if (q4 == 0) s_dxi[4 * (16 * rr + rb) + ax] = dm;
           }
           if (k == 0) {
             // the pinned coefficients move to their boundary values in the first step, and with two robot tiles
