@@ -129,8 +129,8 @@ __device__ __forceinline__ int hb_at(int row, int e) {
 // QP matrix row in LDS: the free coefficients of up to 4 KS in all, padded to whole 16-byte chunks.
 __host__ __device__ constexpr int qp_row(int KS) { return (4 * KS - 6 + 3) & ~3; }
 struct FastLds {
-  int xi, lam, xb, xprev, corr, pairs, mx, dxi, cm, qp, hb, tiles, per_wave, total;
-  int xt, ct, bb, plist;   // offsets inside one wave's tile region
+  int xi, lam, xb, xprev, pairs, mx, dxi, qp, hb, tiles, per_wave, total;
+  int xt, ct, bb, plist, thr;   // offsets inside one wave's tile region
 };
 // Pair table and pair lists of a wave's tiles (count, then pair codes i | j << 8) per tile: 32-bit
 // entries with one robot tile, 16-bit with two.
@@ -141,31 +141,32 @@ template <int R> struct PairList { typedef int T; };
 __host__ __device__ constexpr int box_at(int q, int nr) { return (((q * plist_entries(nr) + 1) >> 1) + 3) & ~3; }
 template <> struct PairList<2> { typedef uint16_t T; };
 
+// What the instance (R, KS, MP) fixes comes first, so that most offsets are compile-time constants in the kernel; the
+// state's stride depends on the degree (padded to 4 KS it would cost resident workgroups) and that of a wave's
+// region on its number of time tiles.
 __host__ __device__ inline FastLds fast_lds_plan(const DevCfg& c, int R, int KS, int W, int MP) {
-  const int nr = 16 * R, Npmax = nr * (nr - 1) / 2, nDm = 3 * c.m * nr;
+  const int nr = 16 * R, Npmax = nr * (nr - 1) / 2, mfx = 4 * KS - 6;
+  const int nst = 3 * c.m * nr;
   FastLds p;
   int o = 0;
-  // (two robot tiles: the previous iterate of the final residual lives in xi_out)
-  p.xi = o; o += nDm;                      // [axis][coefficient][16R robots], zero past the swarm
-  p.lam = o; o += nDm;
-  p.xb = o; o += nDm;                      // (two robot tiles: with the first-step correction for step 0)
-  p.xprev = o; o += R == 1 ? nDm : 0;
-  p.corr = o; o += R == 1 ? 3 * c.mf * nr : 0;   // first-step correction [axis][f][16R robots]
-  p.pairs = o; o += R == 2 ? 0 : Npmax;  // (two robot tiles: in the pair-list regions)
   p.mx = o; o += 2 * 3 * nr;               // [evaluation parity][v, a, workspace][robot]: largest squares
-  p.cm = o; o += 3 * 64;                   // per axis and tail lane: max |coefficient| over the iterates
-  o = (o + 3) & ~3;
-  p.dxi = o; o += 4 * nr;                  // [robot][axis (, pad)]: max |change| of a free coefficient
-  p.qp = o; o += 2 * c.mf * qp_row(KS);    // X1, X01: rows of free coefficients, zero-padded
-  o = (o + 3) & ~3;
+  p.dxi = o; o += 4 * nr;                  // [robot]: max |change| of a free coefficient per axis, max |coefficient| over the iterates (bits)
+  p.qp = o; o += 2 * mfx * qp_row(KS);     // X1, X01: rows of free coefficients, zero-padded
   p.hb = o; o += MP ? 3 * nr * hb_row(R) : 0; // 16-bit S1 B operands: [axis][robot][hi x16, lo x16 (, pad)]
+  p.pairs = o; o += R == 2 ? 0 : Npmax;    // (two robot tiles: in the pair-list regions)
+  // (two robot tiles: the previous iterate of the final residual lives in xi_out)
+  p.xi = o; o += nst;                      // [axis][coefficient][16R robots], zero past the swarm
+  p.lam = o; o += nst;
+  p.xb = o; o += nst;                      // (two robot tiles: with the first-step correction for step 0)
+  p.xprev = o; o += R == 1 ? nst : 0;      // first-step correction until step 0, the previous iterate from the last step
   o = (o + 3) & ~3;                        // 16-byte alignment of the tile buffers
   p.xt = 0;
   p.ct = 3 * nr * 16;
   // (two robot tiles: the boxes of tile q sit at the first 16-byte boundary after the pair lists of
   // tiles 0 .. q - 1, see box_at; those of the last tile run past the lists by at most 12 words)
   p.bb = R == 2 ? 0 : 6 * nr * 16;
-  p.plist = R == 2 ? 6 * nr * 16 : p.bb + box_row(R) * nr;   // per tile of the wave: [count, pairs...] kept across iterations
+  p.thr = R == 2 ? 6 * nr * 16 : p.bb + box_row(R) * nr;   // per tile of the wave, of at most 8 (see s_thr)
+  p.plist = p.thr + 8;                     // per tile of the wave: [count, pairs...] kept across iterations
   const int NT = (c.H + 15) / 16, TQ = (NT + W - 1) / W;
   const int pw = p.plist + (R == 2 ? (TQ * plist_entries(nr) + 1) / 2 + 12 : TQ * plist_entries(nr));
   p.per_wave = (pw + 3) & ~3;
@@ -211,6 +212,20 @@ __device__ __forceinline__ float group_sum(float v) {
   if constexpr (NR == 32) {
     const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  }
+  return v;
+}
+
+// Maximum over aligned groups of NR (16 or 32) lanes; every lane of a group gets it.
+template <int NR>
+__device__ __forceinline__ float group_max(float v) {
+  v = fmaxf(v, dpp<0xB1>(v));
+  v = fmaxf(v, dpp<0x4E>(v));
+  v = fmaxf(v, dpp<0x141>(v));
+  v = fmaxf(v, dpp<0x140>(v));
+  if constexpr (NR == 32) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
   }
   return v;
 }
@@ -331,7 +346,6 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
     float* sxb = smem + L.xb;
     float* sxprev = smem + L.xprev;
     float* sdbar = smem + L.tiles;         // (set-up only)
-    float* scorr = smem + L.corr;
     // pair table, lexicographic (i, j), i < j: shared with one robot tile; with two, each wave's copy
     // in its pair-list region, written where needed (set-up, final residual)
     typedef typename PairList<R>::T PT;
@@ -346,7 +360,6 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
     // of one evaluation is read by the next iteration and cleared in its tail
     uint32_t* s_mx = reinterpret_cast<uint32_t*>(smem + L.mx);
     float* s_dxi = smem + L.dxi;
-    float* s_cm = smem + L.cm;
     // LDS word of element q of a sample ([robot][axis][coefficient]); the division by m <= 16 is exact for
     // the q < 1536 of a sample
     const unsigned minv = (65535u + m) / m;
@@ -365,6 +378,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
       shb[hb_at<R>(d * NR + robot, 16 + kk)] = lo;
     };
     float* wbuf = smem + L.tiles + wave * L.per_wave;
+    // per tile of the wave: how far the summed drift may grow before some listed pair can collide
+    float* s_thr = wbuf + L.thr;
     float* Xt = wbuf + L.xt;
     float* Ct = wbuf + L.ct;
     float* bb = wbuf + L.bb;
@@ -381,9 +396,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
     // QP matrices X1 (relative motion) and X01 (mean motion minus relative), [matrix][f][f2] (zero-padded)
     constexpr int QR = qp_row(KS), MFX = 4 * KS - 6;   // (MFX: free coefficients per robot-axis, at most)
     float* sX1 = smem + L.qp;
-    for (int q = tid; q < 2 * mf * QR; q += nthr) {
-      const int f2 = q % QR, f = (q / QR) % mf, mat = q / (QR * mf);
-      sX1[q] = f2 < mf ? (mat == 0 ? X1 : X01)[f * mf + f2] : 0.0f;
+    for (int q = tid; q < 2 * MFX * QR; q += nthr) {
+      const int f2 = q % QR, f = (q / QR) % MFX, mat = q / (QR * MFX);
+      sX1[q] = f < mf && f2 < mf ? (mat == 0 ? X1 : X01)[f * mf + f2] : 0.0f;
     }
     for (int q = tid; q < nRm; q += nthr) sxi[q] = slam[q] = sxb[q] = 0.0f;   // (phantom robots stay zero)
     // basis operand tables: fp32 [tile][basis][S1 A operand, S4 B operand (x rho)][lane],
@@ -419,14 +434,12 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
       const int iters_s = in_flag < 0 ? 0 : iters;
       __syncthreads();
       // bound on |coefficient| over the iterates: the initial one and the pinned values
-      for (int q = tid; q < 3 * 64; q += nthr) {
-        const int d = q >> 6, rb = q & 15, q4 = (q >> 4) & 3;
+      for (int q = tid; q < 3 * n; q += nthr) {
+        const int robot = q / 3, d = q - 3 * robot;
         float cmx = 0.0f;
-        for (int robot = rb; robot < n; robot += 16) {
-          for (int kk = q4; kk < m; kk += 4) cmx = fmaxf(cmx, fabsf(sxi[coef_at(robot, d, kk)]));
-          for (int r = q4; r < kNFix; r += 4) cmx = fmaxf(cmx, fabsf(pinned(robot * 3 + d, r)));
-        }
-        s_cm[q] = cmx;
+        for (int kk = 0; kk < m; ++kk) cmx = fmaxf(cmx, fabsf(sxi[coef_at(robot, d, kk)]));
+        for (int r = 0; r < kNFix; ++r) cmx = fmaxf(cmx, fabsf(pinned(q, r)));
+        atomicMax(reinterpret_cast<uint32_t*>(s_dxi) + 4 * robot + 3, __float_as_uint(cmx));
       }
       if constexpr (MP != 0) {
         // one thread per (axis, robot, coefficient) of the padded operand rows (zeros outside)
@@ -453,7 +466,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           acc = fmaf(Rfx[f * kNFix + r], dl, acc);
         }
         if constexpr (LEAN) sxb[coef_at(robot, d, 3 + f)] += acc;   // step 0 reads xi_bar + correction
-        else scorr[(d * mf + f) * NR + robot] = acc;
+        else sxprev[coef_at(robot, d, 3 + f)] = acc;
       }
       __syncthreads();
       // bound-ball drift tracking, lane = robot, identical in every wave: margin to the bound at
@@ -471,6 +484,10 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
       // this lane's share of the fixed-point residual sum_k ||xi^{k+1} - xi^k||^2 +
       // ||lambda^{k+1} - lambda^k||^2 (multiplier/QP-step lanes; lambda changes by -g)
       float fpsum = 0.0f;
+      // summed bound on the change of any position (Euclidean) since the lists were built, and the rounding of a pair's
+      // separation (both positions, at the evaluation and later; see the list margins)
+      float drift = 0.0f, ptol = 0.0f;
+      const float smin = (float)(c.a < c.b ? c.a : c.b);
       const float skx = (float)(c.skin * c.a) * 0.999f, skz = (float)(c.skin * c.b) * 0.999f;
 
       for (int k = 0; k < iters_s; ++k) {
@@ -490,10 +507,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           }
         }
         if ((resid_out || status_out) && k == iters_s - 1) {
-          if constexpr (LEAN)   // overwritten with the result at the end
+          if constexpr (LEAN)   // overwritten with the result at the end (one robot tile: kept by the step)
             for (int q = tid; q < nDm; q += nthr) xi_out[coef + q] = sxi[state_at(q)];
-          else
-            for (int q = tid; q < nRm; q += nthr) sxprev[q] = sxi[q];
         }
         // Velocity/acceleration at every grid time move by at most L * ||max_k |d xi_{i,d,k}| ||_2
         // per step (L = max_t sum_k |basis row|).  While the accumulated drift of every robot stays
@@ -504,6 +519,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         const bool clear_mx = (prev_eval | ws_prev) != 0;   // the other buffer holds the last evaluation
         int eval_flags = 3;
         bool rebuild = true, ws_eval = false;
+        float cmx;   // max |coefficient| of robot lane
         {
           // margins to the bounds measured by the previous iteration if it evaluated them
           // (every wave computes the same values).  The hardware square root (1 ulp) serves: the
@@ -523,10 +539,12 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             if constexpr (WS)
               if (ws_prev) wsl = 1.0f - __builtin_amdgcn_sqrtf(__uint_as_float(pm[2 * NR]));
           }
+          cmx = dx[3];
           const float dn = __builtin_amdgcn_sqrtf(dx[0] * dx[0] + dx[1] * dx[1] + dx[2] * dx[2]);
           px_ += dx[0];
           py_ += dx[1];
           pz_ += dx[2];
+          drift = fmaf(drift, 1.8e-7f, drift + 1.0001f * group_max<NR>(dn));   // (rounded up: small steps count)
           dv += Lv * dn;
           da += La * dn;
           // ||M_w^{-1} (sum of steps)|| <= sum of ||M_w^{-1} step|| (triangle inequality)
@@ -555,7 +573,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           if constexpr (WS) ws_prev = ws_eval;
         }
         prev_eval = eval_flags;
-        if (rebuild) px_ = py_ = pz_ = 0.0f;
+        if (rebuild) px_ = py_ = pz_ = drift = 0.0f;
         // Margins of the broad phase: twice the drift margin per axis, plus the rounding of the
         // positions.  A computed position is a rounded convex combination of its coefficients, off by
         // at most ~1.2e-5 of the largest |coefficient| (16-bit split products; fp32 far less); 2^-12
@@ -564,10 +582,24 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         // iteration.
         float mgx = 0.0f, mgz = 0.0f;
         if (rebuild) {
-          const float cm = fmaxf(fmaxf(s_cm[lane], s_cm[64 + lane]), s_cm[128 + lane]);
-          const float tol = 2.44140625e-4f * (wave_max(cm) + fmaxf(skx, skz));
+          const float tol = 2.44140625e-4f * (wave_max(cmx) + fmaxf(skx, skz));
           mgx = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(2.0f * skx + tol)));
           mgz = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(2.0f * skz + tol)));
+          ptol = (MP == 0 ? 0.03125f : 0.5f) * tol;   // (four positions of up to 3e-7 or 1.2e-5 of the largest |coefficient|)
+        }
+        // Time tiles this wave evaluates.  After an evaluation that found no residual, the least ||s|| of the
+        // tile's listed pairs (their separation in units of the safety distance) exceeds 1 by a margin, and a
+        // pair closes by at most twice the drift of a position: until the drift since then reaches half the
+        // margin, less the rounding, every residual of the tile is exactly zero and the tile is skipped.  Once
+        // the early iterations have separated the robots, most tiles are: over 300 iterations a quarter of the tiles
+        // is evaluated with 16 robots (1024 samples, bf16: 1.38 -> 1.26 ms), under half with 32 (4096 samples: 18.4
+        // ms before and after, the step bounds it) and few with 8 robots x 4 samples (318 -> 272 us).
+        unsigned need;
+        {
+          const bool force = rebuild || eval_flags != 0 || (WS && ws_eval);
+          const int nq = wave < NT ? (NT - 1 - wave) / W + 1 : 0;
+          const float th = s_thr[lane < TQ ? lane : 0];
+          need = (unsigned)ballot(lane < nq && (force || drift > th));
         }
         // S1 B operand: xi^T, lane (col, grp) holds robot col, coefficient 4 s + grp
         float bx[MP == 0 ? R : 1][3][KS];
@@ -662,14 +694,15 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         // position operands of the wave's first tile; each tile prefetches those of its next one
         float4 pa = {0.0f, 0.0f, 0.0f, 0.0f}, pb = {0.0f, 0.0f, 0.0f, 0.0f};
         uint4 pu1 = {0u, 0u, 0u, 0u}, pu2 = {0u, 0u, 0u, 0u};
-        if (wave < NT) {
-          if constexpr (MP == 0) pa = a32c[((wave * 3) * 2) * 64 + lane];
+        auto fetch = [&](int tau) {
+          if constexpr (MP == 0) pa = a32c[((tau * 3) * 2) * 64 + lane];
           else {
-            pu1 = a16c[((wave * 3) * 2) * 64 + lane];
-            pu2 = a16c[((wave * 3) * 2 + 1) * 64 + lane];
+            pu1 = a16c[((tau * 3) * 2) * 64 + lane];
+            pu2 = a16c[((tau * 3) * 2 + 1) * 64 + lane];
           }
-          pb = a32c[((wave * 3) * 2 + 1) * 64 + lane];
-        }
+          pb = a32c[((tau * 3) * 2 + 1) * 64 + lane];
+        };
+        if (need != 0) fetch(wave + W * __builtin_ctz(need));
 
         // Issue priority (one robot tile): from the end of a wave's tiles through the partial write,
         // the barriers, the multiplier/QP step and the flags up to here, a wave runs at priority 2
@@ -682,10 +715,10 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           if ((NT - 1 - wave) / W + 1 == TQ) __builtin_amdgcn_s_setprio(1);
           else __builtin_amdgcn_s_setprio(0);
         }
-#pragma unroll 1
-        for (int q = 0; q < TQ; ++q) {
+        while (need != 0) {
+          const int q = __builtin_ctz(need);
+          need &= need - 1;
           const int tau = wave + W * q;
-          if (tau >= NT) break;
           const int t0 = 16 * tau;
           const int nt = min(16, H - t0);
           const float4 ca = pa, cb = pb;
@@ -699,15 +732,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           const int tsh = nt <= 4 ? 2 : (nt <= 8 ? 3 : 4);
           const int tt = lane & ((1 << tsh) - 1), ps = lane >> tsh, ppr = 64 >> tsh;
           const int kept_count = tl[0], kept_first = tl[1 + ps];
-          if (tau + W < NT) {
-            const int nx = tau + W;
-            if constexpr (MP == 0) pa = a32c[((nx * 3) * 2) * 64 + lane];
-            else {
-              pu1 = a16c[((nx * 3) * 2) * 64 + lane];
-              pu2 = a16c[((nx * 3) * 2 + 1) * 64 + lane];
-            }
-            pb = a32c[((nx * 3) * 2 + 1) * 64 + lane];
-          }
+          if (need != 0) fetch(wave + W * __builtin_ctz(need));
           bool ws_nz = false;   // some workspace residual of the tile is nonzero (wave-uniform)
           // ---- S1 positions -> LDS, per-robot boxes over the tile in registers ----
           // (not needed when the tile's kept pair list is empty and no list or workspace row is
@@ -851,6 +876,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           // narrow phase, one round of pairs per step; the next round's pair codes load meanwhile
           // (most tiles list at most one round)
           bool nzc = false;
+          float near = FLT_MAX;   // least ||s||^2 of this lane's items
           for (int base = 0; base < count; base += ppr) {
             const int slot = base + ps;
             const int pij = pnext;
@@ -861,6 +887,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               const float ry = Xt[tile_at(1 * NR + i, tt)] - Xt[tile_at(1 * NR + j, tt)];
               const float rz = Xt[tile_at(2 * NR + i, tt)] - Xt[tile_at(2 * NR + j, tt)];
               float Rx, Ry, Rz;
+              near = fminf(near, (rx * rx + ry * ry) * ia2 + rz * rz * ib2);
               coll_resid3(rx, ry, rz, ia2, ib2, sb, Rx, Ry, Rz);
               if (Rx != 0.0f || Ry != 0.0f || Rz != 0.0f) {
                 nzc = true;
@@ -873,7 +900,15 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               }
             }
           }
-          if (ws_nz || ballot(nzc) != 0) {
+          const bool hit = ballot(nzc) != 0;
+          {
+            // (a tile without listed pairs needs no evaluation before the next rebuild)
+            float th = hit ? -1.0f : FLT_MAX;
+            if (!hit && count > 0)
+              th = drift + 0.4999f * ((__builtin_amdgcn_sqrtf(-wave_max(-near)) - 1.0f) * smin - ptol);
+            if (lane == 0) s_thr[q] = th;
+          }
+          if (ws_nz || hit) {
             wave_sync();
             const float b4[4] = {cb.x, cb.y, cb.z, cb.w};
 #pragma unroll
@@ -898,7 +933,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           for (int d = 0; d < 3; ++d)
 #pragma unroll
             for (int r = 0; r < KS; ++r) wbuf[((d * R + rr) * KS + r) * 64 + lane] = gacc[rr][d][r];
-        if (grp == 0) {
+        if ((eval_flags != 0 || (WS && ws_eval)) && grp == 0) {
 #pragma unroll
           for (int rr = 0; rr < R; ++rr) {
             uint32_t* pm = s_mx + par * 3 * NR + 16 * rr + col;
@@ -913,18 +948,17 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           for (int q = tid; q < 3 * NR; q += nthr) s_mx[(par ^ 1) * 3 * NR + q] = 0u;
         // Multiplier step and QP step of one axis per wave: lane (rb, q4) holds coefficients q4 + 4 r of robots
         // rb (and 16 + rb).  g = F^T rho R summed over the waves, lambda <- lambda - g,
-        // y = xi_bar - xi + lambda - g (+ the first-step correction, in xi_bar) on the free coefficients, and
+        // y = xi_bar - xi + lambda - g (+ the first-step correction; with two robot tiles it sits in xi_bar) on the free coefficients, and
         // xi_free += X1 y + X01 mean_robots(y).  Every load is issued first and a scheduling barrier keeps the
         // arithmetic after them; y and its means then reach the lanes of a robot through LDS, in this axis'
-        // partials of wave 0, which no other wave reads.  With two lanes of
-        // half-filled waves walking each row the step was a fifth of an iteration with one robot tile and a
-        // third with two (16 robots x 1024 samples, bf16, 300 iterations: 1.37 -> 1.32 ms; 32 robots x 4096:
-        // 19.7 -> 18.3 ms).
+        // partials of wave 0, which no other wave reads.  With two lanes per row, half the waves idle, the step was
+        // a fifth of an iteration with one robot tile and a third with two (16 robots x 1024 samples, bf16, 300
+        // iterations: 1.37 -> 1.32 ms; 32 robots x 4096: 19.7 -> 18.3 ms).
         for (int ax = wave; ax < 3; ax += W) {
           float* gp0 = smem + L.tiles + ax * (R * KS * 64);
           const int q4 = lane >> 4, rb = lane & 15;
           const int e0 = (ax * m + q4) * NR + rb;
-          float xv[R][KS], lf[R][KS], xb[R][KS], gw[R][KS][W];
+          float xv[R][KS], lf[R][KS], xb[R][KS], gs[R][KS];
           constexpr bool EARLY = R == 1;   // (two robot tiles: no registers left to load the matrices ahead)
           f4 x1[EARLY ? KS - 1 : 1][QR / 4], x01[EARLY ? KS - 1 : 1][QR / 4];
 #pragma unroll
@@ -936,16 +970,22 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
               xv[rr][r] = sxi[e];
               lf[rr][r] = slam[e];
               xb[rr][r] = sxb[e];
-#pragma unroll
-              for (int ww = 0; ww < W; ++ww) gw[rr][r][ww] = gp0[ww * L.per_wave + (rr * KS + r) * 64 + lane];
             }
-          float cmax = s_cm[ax * 64 + lane];
+#pragma unroll
+          for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+            for (int r = 0; r < KS; ++r) {
+              gs[rr][r] = gp0[(rr * KS + r) * 64 + lane];
+#pragma unroll
+              for (int ww = 1; ww < W; ++ww) gs[rr][r] += gp0[ww * L.per_wave + (rr * KS + r) * 64 + lane];
+            }
+          const bool last = !LEAN && (resid_out || status_out) && k == iters_s - 1;
           auto qp_rows = [&](int r, f4 (&a)[QR / 4], f4 (&b)[QR / 4]) {   // (rows of a free coefficient, else any)
             const int fc = max(0, min(4 * r + q4 - 3, mf - 1));
 #pragma unroll
             for (int cc = 0; cc < QR / 4; ++cc) {
               a[cc] = *reinterpret_cast<const f4*>(sX1 + fc * QR + 4 * cc);
-              b[cc] = *reinterpret_cast<const f4*>(sX1 + (mf + fc) * QR + 4 * cc);
+              b[cc] = *reinterpret_cast<const f4*>(sX1 + (MFX + fc) * QR + 4 * cc);
             }
           };
 #pragma unroll
@@ -959,14 +999,11 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             const int kk = 4 * r + q4;
 #pragma unroll
             for (int rr = 0; rr < R; ++rr) {
-              float g = gw[rr][r][0];
-#pragma unroll
-              for (int ww = 1; ww < W; ++ww) g += gw[rr][r][ww];
-              gw[rr][r][0] = g;
+              const float g = gs[rr][r];
               lf[rr][r] -= g;
               float yv = xb[rr][r] - xv[rr][r] + lf[rr][r] - g;
               if constexpr (!LEAN)
-                if (k == 0 && kk >= 3 && kk < m - 3) yv += scorr[(ax * mf + kk - 3) * NR + rb];
+                if (k == 0 && kk >= 3 && kk < m - 3) yv += sxprev[e0 + 4 * r * NR + 16 * rr];
               const float y = (kk >= 3 && kk < m - 3 && 16 * rr + rb < n) ? yv : 0.0f;
               sy[kk * NR + 16 * rr + rb] = y;
               const float t = group_sum<16>(y);
@@ -993,7 +1030,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                 acc[rr][r] = fmaf(b[f2 / 4][f2 % 4], yba[f2], acc[rr][r]);
               }
           };
-          float dmax[R];
+          float dmax[R], cmax[R];
           // new coefficients 4 r + q4 (phantom robots store their zeros)
           auto finish = [&](int r) {
             const int kk = 4 * r + q4;
@@ -1001,12 +1038,12 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             for (int rr = 0; rr < R; ++rr) {
               const bool upd = kk >= 3 && kk < m - 3 && 16 * rr + rb < n;
               if (fpr && 16 * rr + rb < n && kk < m) {
-                fpsum = fmaf(gw[rr][r][0], gw[rr][r][0], fpsum);
+                fpsum = fmaf(gs[rr][r], gs[rr][r], fpsum);
                 if (upd) fpsum = fmaf(acc[rr][r], acc[rr][r], fpsum);
               }
               dmax[rr] = fmaxf(dmax[rr], upd ? fabsf(acc[rr][r]) : 0.0f);
               xb[rr][r] = upd ? xv[rr][r] + acc[rr][r] : xv[rr][r];
-              cmax = fmaxf(cmax, kk < m ? fabsf(xb[rr][r]) : 0.0f);
+              cmax[rr] = fmaxf(cmax[rr], kk < m ? fabsf(xb[rr][r]) : 0.0f);
             }
             if (kk < m) {
 #pragma unroll
@@ -1014,12 +1051,14 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                 const int e = e0 + 4 * r * NR + 16 * rr;
                 sxi[e] = xb[rr][r];
                 slam[e] = lf[rr][r];
+                if constexpr (!LEAN)
+                  if (last) sxprev[e] = xv[rr][r];
                 if constexpr (MP != 0) put_split(16 * rr + rb, ax, kk, xb[rr][r]);
               }
             }
           };
 #pragma unroll
-          for (int rr = 0; rr < R; ++rr) dmax[rr] = 0.0f;
+          for (int rr = 0; rr < R; ++rr) dmax[rr] = cmax[rr] = 0.0f;
 #pragma unroll
           for (int r = 0; r < KS; ++r)
 #pragma unroll
@@ -1037,11 +1076,11 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           }
 #pragma unroll
           for (int r = EARLY ? 0 : KS - 1; r < KS; ++r) finish(r);
-          s_cm[ax * 64 + lane] = cmax;
 #pragma unroll
           for (int rr = 0; rr < R; ++rr) {
             const float dm = grp_max(dmax[rr]);
             if (q4 == 0) s_dxi[4 * (16 * rr + rb) + ax] = dm;
+            atomicMax(reinterpret_cast<uint32_t*>(s_dxi) + 4 * (16 * rr + rb) + 3, __float_as_uint(cmax[rr]));
           }
           if (k == 0) {
             // the pinned coefficients move to their boundary values in the first step, and with two robot tiles
