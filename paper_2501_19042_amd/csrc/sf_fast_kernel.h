@@ -1109,60 +1109,72 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
       }
 
       // ---- primal residual of the last step (dense over pairs) ----
+      // Bound by the latency of its chains: operand splits, products, pair rounds.  The operands of both iterates
+      // are formed once, each tile's basis operands load together and the pair rounds go two at a time (13 robots
+      // in a workspace, 333 samples, 60 iterations, fp16: 278 -> 270 us for the whole solve).
       float rmax = 0.0f;   // its largest block norm (thread 0)
       if (resid_out || status_out) {
         float ss = 0.0f, mx = 0.0f;
         if (iters_s > 0) {
-          if constexpr (R == 2) {
-            // the wave's pair lists are no longer needed (lane index from an opaque copy, so that
-            // nothing of the fill is computed ahead of the iterations)
-            int ln = threadIdx.x & 63;
-            asm volatile("" : "+v"(ln));
-            fill_pairs(ln, 64);
+          // (lane index from an opaque copy, so that nothing is computed ahead of the iterations)
+          int ln = threadIdx.x & 63;
+          asm volatile("" : "+v"(ln));
+          const int lane = ln, col = ln & 15, grp = ln >> 4;
+          if constexpr (R == 2) {   // the wave's pair lists are no longer needed
+            fill_pairs(lane, 64);
             wave_sync();
           }
-          // One basis product of a tile for the iterate in `src` (previous or new).  The B operands
-          // are formed per product (this runs once per solve), so that only one iterate's
-          // products are live at a time.
-          // (prev: the previous iterate, in LDS or, with two robot tiles, in xi_out)
-          auto prod = [&](bool prev, int tau, int b, f4 (&Y)[R][3]) {
-            const float* src = prev ? (LEAN ? xi_out + coef : sxprev) : sxi;
-            const bool glob = LEAN && prev;
+          // B operands of the basis products for the previous and the new iterate, formed once for all tiles
+          // (previous: in LDS or, with two robot tiles, in xi_out; two robot tiles in fp32: the new one is read
+          // per product, or they would spill)
+          constexpr int HELD = R == 2 && MP == 0 ? 1 : 2;
+          typedef typename Half<MP == 0 ? 1 : MP>::V V;
+          float b32[HELD][MP == 0 ? R : 1][3][KS];
+          V b16[2][MP == 0 ? 1 : R][3][2];
+#pragma unroll
+          for (int it = 0; it < HELD; ++it) {
+            const float* src = it == 0 ? (LEAN ? xi_out + coef : sxprev) : sxi;
+            const bool glob = LEAN && it == 0;
             const int sr = glob ? 3 * m : 1, sd = glob ? m : m * NR, sk = glob ? 1 : NR;
-            if constexpr (MP == 0) {
-              const float4 av = a32c[((tau * 3 + b) * 2) * 64 + lane];
-              const float a1[4] = {av.x, av.y, av.z, av.w};
 #pragma unroll
-              for (int rr = 0; rr < R; ++rr)
+            for (int rr = 0; rr < R; ++rr)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                  f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+              for (int d = 0; d < 3; ++d) {
+                const int robot = 16 * rr + col;
+                if constexpr (MP == 0) {
 #pragma unroll
                   for (int s = 0; s < KS; ++s) {
-                    const int robot = 16 * rr + col, kk = 4 * s + grp;
-                    const float v = (robot < n && kk < m) ? src[robot * sr + d * sd + kk * sk] : 0.0f;
+                    const int kk = 4 * s + grp;
+                    b32[it][rr][d][s] = (robot < n && kk < m) ? src[robot * sr + d * sd + kk * sk] : 0.0f;
+                  }
+                } else {
+                  split_xi<MP>(src + (robot < n ? robot * sr + d * sd : 0), sk, robot < n, m, grp, b16[it][rr][d][0],
+                               b16[it][rr][d][1]);
+                }
+              }
+          }
+          // one basis product of a tile for an iterate
+          auto prod = [&](int it, const uint4 (&au)[2], f4 (&Y)[R][3]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr)
+#pragma unroll
+              for (int d = 0; d < 3; ++d) {
+                f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+                if constexpr (MP == 0) {
+                  const f4 a1 = __builtin_bit_cast(f4, au[0]);
+#pragma unroll
+                  for (int s = 0; s < KS; ++s) {
+                    // (past m the A operand is zero and the words read hold finite state, as do phantom robots)
+                    const float v = it < HELD ? b32[it < HELD ? it : 0][rr][d][s]
+                                              : sxi[(d * m + 4 * s + grp) * NR + 16 * rr + col];
                     acc = mfma4(a1[s], v, acc);
                   }
-                  Y[rr][d] = acc;
+                } else {
+                  acc = mfma16(__builtin_bit_cast(V, au[0]), b16[it][rr][d][0], acc);
+                  acc = mfma16(__builtin_bit_cast(V, au[1]), b16[it][rr][d][1], acc);
                 }
-            } else {
-              typedef typename Half<MP>::V V;
-              const uint4* at = a16c + ((tau * 3 + b) * 2) * 64 + lane;
-              const V A1 = __builtin_bit_cast(V, at[0]);
-              const V A2 = __builtin_bit_cast(V, at[64]);
-#pragma unroll
-              for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                  V h1, h2;
-                  const int robot = 16 * rr + col;
-                  split_xi<MP>(src + (robot < n ? robot * sr + d * sd : 0), sk, robot < n, m, grp, h1, h2);
-                  f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                  acc = mfma16(A1, h1, acc);
-                  acc = mfma16(A2, h2, acc);
-                  Y[rr][d] = acc;
-                }
-            }
+                Y[rr][d] = acc;
+              }
           };
 #pragma unroll 1
           for (int q = 0; q < TQ; ++q) {
@@ -1170,12 +1182,22 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             if (tau >= NT) break;
             const int t0 = 16 * tau;
             const int nt = min(16, H - t0);
-#pragma unroll 1
+            uint4 au[3][2];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+              if constexpr (MP == 0) {
+                au[b][0] = __builtin_bit_cast(uint4, a32c[((tau * 3 + b) * 2) * 64 + lane]);
+              } else {
+                au[b][0] = a16c[((tau * 3 + b) * 2) * 64 + lane];
+                au[b][1] = a16c[((tau * 3 + b) * 2 + 1) * 64 + lane];
+              }
+            }
+#pragma unroll
             for (int b = 0; b < 3; ++b) {
               if (b > 0 && !(b == 1 ? c.vel_on : c.acc_on)) continue;
               const float lim = b == 1 ? vmax : amax;
               f4 Y[R][3];
-              prod(true, tau, b, Y);
+              prod(0, au[b], Y);
               if (b == 0) {
 #pragma unroll
                 for (int rr = 0; rr < R; ++rr)
@@ -1197,7 +1219,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                   }
               }
               f4 Yn[R][3];
-              prod(false, tau, b, Yn);
+              prod(1, au[b], Yn);
               if (b == 0) {
 #pragma unroll
                 for (int rr = 0; rr < R; ++rr)
@@ -1238,11 +1260,18 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                 }
             }
             wave_sync();
-            for (int base = 0; base < Np; base += 4) {
-              const int slot = base + grp;
-              if (slot < Np && col < nt) {
-                const int pij = spairs[slot];
+            // four pairs of up to 16 times per round, two rounds in flight and the codes of the next two loading
+            // meanwhile; a lane adds its pairs in order.
+            int next[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) next[u] = spairs[max(0, min(4 * u + grp, Np - 1))];
+            for (int base = 0; base < Np; base += 8) {
+              float nrm[2];
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                const int pij = next[u];
                 const int i = pij & 255, j = pij >> 8;
+                next[u] = spairs[min(base + 8 + 4 * u + grp, Np - 1)];
                 float rp[3], rn[3];
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
@@ -1252,9 +1281,13 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                 float Rx, Ry, Rz;
                 coll_resid3(rp[0], rp[1], rp[2], ia2, ib2, sb, Rx, Ry, Rz);
                 const float px = rn[0] - (rp[0] - Rx), py = rn[1] - (rp[1] - Ry), pz = rn[2] - (rp[2] - Rz);
-                const float nrm = px * px + py * py + pz * pz;
-                ss += nrm;
-                mx = fmaxf(mx, nrm);
+                nrm[u] = px * px + py * py + pz * pz;
+              }
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                const float v = base + 4 * u + grp < Np && col < nt ? nrm[u] : 0.0f;
+                ss += v;
+                mx = fmaxf(mx, v);
               }
             }
             wave_sync();
