@@ -12,7 +12,8 @@
 //     S2  collision residuals (alpha/beta/d steps in radial form): positions go to LDS; per
 //         tile, a list of the pairs whose position boxes come within the safety distance plus a
 //         margin, rebuilt only when some robot may have moved by more than the margin; the
-//         listed pair-times are projected and scattered into an LDS accumulator.
+//         listed pair-times are projected and scattered into an LDS accumulator.  A tile without
+//         a residual is left out until some listed pair may have closed.
 //     S4  g += P_b^T (rho_b R_b) as MFMA products, only for tiles with a nonzero residual; the
 //         S1 output layout is exactly the A-operand layout this product needs.
 //   barrier; tail (one wave per axis): multiplier step, and the structured QP step of eq. (xi_step) on the
