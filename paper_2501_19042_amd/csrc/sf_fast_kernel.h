@@ -604,9 +604,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         }
         // S1 B operand: xi^T, lane (col, grp) holds robot col, coefficient 4 s + grp
         float bx[MP == 0 ? R : 1][3][KS];
-        // (two robot tiles at two waves per SIMD: the 16-bit operands are re-read from LDS per
-        // product instead of held across the tiles, 48 registers fewer)
-        constexpr bool HBR = R == 2 && W >= 3;
+        // (two robot tiles at two waves per SIMD, and the workspace instances: the 16-bit operands are re-read
+        // from LDS per product instead of held across the tiles, 48 or 24 registers fewer)
+        constexpr bool HBR = R == 1 ? MP != 0 && WS != 0 : W >= 3;
         // (two robot tiles: offsets of this lane's hi and lo chunks from the first row of its robot
         // tile and axis, robot col, entries 8 (grp & 1) and 16 + 8 (grp & 1); see hb_at)
         const int hb_hi = hb_at<R>(col, 8 * (grp & 1)), hb_lo = hb_at<R>(col, 16 + 8 * (grp & 1));
@@ -1126,12 +1126,12 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             wave_sync();
           }
           // B operands of the basis products for the previous and the new iterate, formed once for all tiles
-          // (previous: in LDS or, with two robot tiles, in xi_out; two robot tiles in fp32: the new one is read
-          // per product, or they would spill)
-          constexpr int HELD = R == 2 && MP == 0 ? 1 : 2;
+          // (previous: in LDS or, with two robot tiles, in xi_out; one robot tile in 16 bits and two in fp32: the
+          // new one is read per product, which keeps the registers within the budget)
+          constexpr int HELD = (R == 2) == (MP == 0) ? 1 : 2;
           typedef typename Half<MP == 0 ? 1 : MP>::V V;
           float b32[HELD][MP == 0 ? R : 1][3][KS];
-          V b16[2][MP == 0 ? 1 : R][3][2];
+          V b16[HELD][MP == 0 ? 1 : R][3][2];
 #pragma unroll
           for (int it = 0; it < HELD; ++it) {
             const float* src = it == 0 ? (LEAN ? xi_out + coef : sxprev) : sxi;
@@ -1171,8 +1171,17 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
                     acc = mfma4(a1[s], v, acc);
                   }
                 } else {
-                  acc = mfma16(__builtin_bit_cast(V, au[0]), b16[it][rr][d][0], acc);
-                  acc = mfma16(__builtin_bit_cast(V, au[1]), b16[it][rr][d][1], acc);
+                  V hi, lo;
+                  if (it < HELD) {
+                    hi = b16[it < HELD ? it : 0][rr][d][0];
+                    lo = b16[it < HELD ? it : 0][rr][d][1];
+                  } else {
+                    const HE* hrow = shb + (d * NR + 16 * rr) * (2 * hb_row(R));
+                    hi = __builtin_bit_cast(V, *reinterpret_cast<const uint4*>(hrow + hb_at<R>(col, 8 * (grp & 1))));
+                    lo = __builtin_bit_cast(V, *reinterpret_cast<const uint4*>(hrow + hb_at<R>(col, 16 + 8 * (grp & 1))));
+                  }
+                  acc = mfma16(__builtin_bit_cast(V, au[0]), hi, acc);
+                  acc = mfma16(__builtin_bit_cast(V, au[1]), lo, acc);
                 }
                 Y[rr][d] = acc;
               }
@@ -1388,6 +1397,12 @@ fast_batched_kernel(FastArgs A, int* __restrict__ queue) {
 // per sample (256 VGPRs; two workgroups per CU by LDS, six or eight waves) and 1 for two (the whole
 // register file).
 constexpr int waves_per_simd(int R, int MP, int W) { return R == 1 ? 3 : (W >= 3 ? 2 : 1); }
+// Register budget, as waves per SIMD.  A CU takes four samples of three waves each.  At 168 registers they fill all
+// twelve wave slots, and after a kernel with other workgroups the last sample often finds no slots of its shape, which
+// costs another round: 16 robots x 1024 samples, 319 iterations, after a feasibility check took 1.75 ms against
+// 1.22.  At 128 registers slots are left over: 1.24 ms in any order (fp32 needs no more by itself).  The plans count
+// waves_per_simd.
+constexpr int reg_waves(int R, int MP, int W) { return R == 1 && MP != 0 ? 4 : waves_per_simd(R, MP, W); }
 
 FastArgs make_fast_args(const LaunchArgs& a, const float* tab32, const uint4* a16) {
   FastArgs f;
@@ -1403,7 +1418,7 @@ FastArgs make_fast_args(const LaunchArgs& a, const float* tab32, const uint4* a1
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_instance(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
-  auto kern = fast_project_kernel<R, KS, W, MP, waves_per_simd(R, MP, W), WS>;
+  auto kern = fast_project_kernel<R, KS, W, MP, reg_waves(R, MP, W), WS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes[W - 2][MP]);
   if (e != hipSuccess) return e;
@@ -1414,7 +1429,7 @@ hipError_t launch_instance(const FastPlan& p, const LaunchArgs& a, const float* 
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_segments_instance(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
-  auto kern = fast_segments_kernel<R, KS, W, MP, waves_per_simd(R, MP, W), WS>;
+  auto kern = fast_segments_kernel<R, KS, W, MP, reg_waves(R, MP, W), WS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes[W - 2][MP]);
   if (e != hipSuccess) return e;
@@ -1440,7 +1455,7 @@ hipError_t launch_segments_mp(const FastPlan& p, const LaunchArgs& a, const floa
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_class(const FastClass& C, const FastArgs& f, int grid, int* queue, hipStream_t stream) {
-  auto kern = fast_batched_kernel<R, KS, W, MP, waves_per_simd(R, MP, W), WS>;
+  auto kern = fast_batched_kernel<R, KS, W, MP, reg_waves(R, MP, W), WS>;
   const size_t lds = C.lds_bytes[W - 2][MP];
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
