@@ -284,9 +284,25 @@ struct FastArgs {
   int fpr;               // accumulate the fixed-point residual sum (resid_out is [S][3])
 };
 
-// The whole solve of one work item (its samples) by one workgroup.  WS: the instance carries the
-// workspace rows (evaluated for the configs that have them).
-template <int R, int KS, int W, int MP, int WS>
+// Target waves per SIMD (the register budget): 3 with one robot tile (168 VGPRs; three waves per
+// sample then keep four samples per CU resident); with two robot tiles 2 for three or four waves
+// per sample (256 VGPRs; two workgroups per CU by LDS, six or eight waves) and 1 for two (the whole
+// register file).
+constexpr int waves_per_simd(int R, int MP, int W) { return R == 1 ? 3 : (W >= 3 ? 2 : 1); }
+// Register budget, as waves per SIMD.  A CU takes four samples of three waves each.  At 168 registers they fill all
+// twelve wave slots, and after a kernel with other workgroups the last sample often finds no slots of its shape, which
+// costs another round: 16 robots x 1024 samples, 319 iterations, after a feasibility check took 1.75 ms against
+// 1.22.  At 128 registers slots are left over: 1.24 ms in any order (fp32 needs no more by itself).  The 16-bit
+// instances of up to 12 coefficients fit that with 5-12 spills.  Those of 13 to 16 do not: they
+// spilled 66-95 registers, most of them inside the iteration (16 robots, degree 13, bf16, 100 iterations: 1024
+// samples 1.76 ms at 128 registers, 0.85 at 168).  The plans count waves_per_simd.
+constexpr int reg_waves(int R, int KS, int MP, int W) {
+  return R == 1 && MP != 0 && KS <= 3 ? 4 : waves_per_simd(R, MP, W);
+}
+
+// The whole solve of one work item (its samples) by one workgroup.  WPE: the register budget, as waves per SIMD.
+// WS: the instance carries the workspace rows (evaluated for the configs that have them).
+template <int R, int KS, int W, int MP, int WPE, int WS>
 __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem) {
   const DevCfg* __restrict__ cfgs = A.cfgs;
   const float* __restrict__ tab = A.tab;
@@ -308,6 +324,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
   const bool fpr = A.fpr != 0;
   const int rw = fpr ? 3 : 2;            // resid_out columns
   constexpr int NR = 16 * R;
+  constexpr bool SLIM = WPE > 3;         // 128 registers: fewer operands held
   constexpr int PR = (NR * (NR - 1) / 2 + 63) / 64;   // 64-pair rounds of the broad phase
   // two robot tiles: no LDS copy of the previous iterate or of the first-step correction (see the plan)
   constexpr bool LEAN = R == 2;
@@ -604,9 +621,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         }
         // S1 B operand: xi^T, lane (col, grp) holds robot col, coefficient 4 s + grp
         float bx[MP == 0 ? R : 1][3][KS];
-        // (two robot tiles at two waves per SIMD, and the workspace instances: the 16-bit operands are re-read
-        // from LDS per product instead of held across the tiles, 48 or 24 registers fewer)
-        constexpr bool HBR = R == 1 ? MP != 0 && WS != 0 : W >= 3;
+        // (two robot tiles at two waves per SIMD, and the workspace instances at 128 registers: the 16-bit
+        // operands are re-read from LDS per product instead of held across the tiles, 48 or 24 registers fewer)
+        constexpr bool HBR = R == 1 ? SLIM && WS != 0 : W >= 3;
         // (two robot tiles: offsets of this lane's hi and lo chunks from the first row of its robot
         // tile and axis, robot col, entries 8 (grp & 1) and 16 + 8 (grp & 1); see hb_at)
         const int hb_hi = hb_at<R>(col, 8 * (grp & 1)), hb_lo = hb_at<R>(col, 16 + 8 * (grp & 1));
@@ -960,7 +977,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
           const int q4 = lane >> 4, rb = lane & 15;
           const int e0 = (ax * m + q4) * NR + rb;
           float xv[R][KS], lf[R][KS], xb[R][KS], gs[R][KS];
-          constexpr bool EARLY = R == 1;   // (two robot tiles: no registers left to load the matrices ahead)
+          // (two robot tiles or more than 12 coefficients: no registers left to load the matrices ahead; 16 robots of
+          // degree 15, fp32, 100 iterations: 1024 samples 0.76 ms with 6-31 spills, 0.72 with the rows as they come)
+          constexpr bool EARLY = R == 1 && KS <= 3;
           f4 x1[EARLY ? KS - 1 : 1][QR / 4], x01[EARLY ? KS - 1 : 1][QR / 4];
 #pragma unroll
           for (int rr = 0; rr < R; ++rr)
@@ -1126,9 +1145,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
             wave_sync();
           }
           // B operands of the basis products for the previous and the new iterate, formed once for all tiles
-          // (previous: in LDS or, with two robot tiles, in xi_out; one robot tile in 16 bits and two in fp32: the
+          // (previous: in LDS or, with two robot tiles, in xi_out; at 128 registers and with two tiles in fp32 the
           // new one is read per product, which keeps the registers within the budget)
-          constexpr int HELD = (R == 2) == (MP == 0) ? 1 : 2;
+          constexpr int HELD = SLIM || (R == 2 && MP == 0) ? 1 : 2;
           typedef typename Half<MP == 0 ? 1 : MP>::V V;
           float b32[HELD][MP == 0 ? R : 1][3][KS];
           V b16[HELD][MP == 0 ? 1 : R][3][2];
@@ -1348,7 +1367,7 @@ template <int R, int KS, int W, int MP, int WPE, int WS>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 fast_project_kernel(FastArgs A) {
   extern __shared__ __align__(16) float smem[];
-  for (int it = blockIdx.x; it < A.n_items; it += gridDim.x) fast_item<R, KS, W, MP, WS>(A, it, smem);
+  for (int it = blockIdx.x; it < A.n_items; it += gridDim.x) fast_item<R, KS, W, MP, WPE, WS>(A, it, smem);
 }
 
 // Recomputes several checkpoint segments at once for the reverse mode: workgroup (segment, work item) runs
@@ -1369,7 +1388,7 @@ fast_segments_kernel(FastArgs A, int nseg, int64_t seg_in, int64_t seg_out, int 
     B.ckpt += seg * seg_out;
     B.xi_out = B.ckpt + B.iters * 2 * A.ckpt_stride;
     B.lam_out = B.xi_out + A.ckpt_stride;
-    fast_item<R, KS, W, MP, WS>(B, it - seg * A.n_items, smem);
+    fast_item<R, KS, W, MP, WPE, WS>(B, it - seg * A.n_items, smem);
   }
 }
 
@@ -1387,23 +1406,11 @@ fast_batched_kernel(FastArgs A, int* __restrict__ queue) {
     const int it = __builtin_amdgcn_readfirstlane(next);
     __syncthreads();
     if (it >= A.n_items) break;
-    fast_item<R, KS, W, MP, WS>(A, it, smem);
+    fast_item<R, KS, W, MP, WPE, WS>(A, it, smem);
   }
 }
 
 // Kernel instances: R robot tiles of 16, KS k-steps of 4 coefficients, W waves per workgroup.
-// Target waves per SIMD (the register budget): 3 with one robot tile (168 VGPRs; three waves per
-// sample then keep four samples per CU resident); with two robot tiles 2 for three or four waves
-// per sample (256 VGPRs; two workgroups per CU by LDS, six or eight waves) and 1 for two (the whole
-// register file).
-constexpr int waves_per_simd(int R, int MP, int W) { return R == 1 ? 3 : (W >= 3 ? 2 : 1); }
-// Register budget, as waves per SIMD.  A CU takes four samples of three waves each.  At 168 registers they fill all
-// twelve wave slots, and after a kernel with other workgroups the last sample often finds no slots of its shape, which
-// costs another round: 16 robots x 1024 samples, 319 iterations, after a feasibility check took 1.75 ms against
-// 1.22.  At 128 registers slots are left over: 1.24 ms in any order (fp32 needs no more by itself).  The plans count
-// waves_per_simd.
-constexpr int reg_waves(int R, int MP, int W) { return R == 1 && MP != 0 ? 4 : waves_per_simd(R, MP, W); }
-
 FastArgs make_fast_args(const LaunchArgs& a, const float* tab32, const uint4* a16) {
   FastArgs f;
   f.cfgs = a.cfgs; f.tab = tab32; f.a16 = a16; f.probs = a.probs; f.items = a.items; f.n_items = a.n_items;
@@ -1418,7 +1425,7 @@ FastArgs make_fast_args(const LaunchArgs& a, const float* tab32, const uint4* a1
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_instance(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
-  auto kern = fast_project_kernel<R, KS, W, MP, reg_waves(R, MP, W), WS>;
+  auto kern = fast_project_kernel<R, KS, W, MP, reg_waves(R, KS, MP, W), WS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes[W - 2][MP]);
   if (e != hipSuccess) return e;
@@ -1429,7 +1436,7 @@ hipError_t launch_instance(const FastPlan& p, const LaunchArgs& a, const float* 
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_segments_instance(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
-  auto kern = fast_segments_kernel<R, KS, W, MP, reg_waves(R, MP, W), WS>;
+  auto kern = fast_segments_kernel<R, KS, W, MP, reg_waves(R, KS, MP, W), WS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes[W - 2][MP]);
   if (e != hipSuccess) return e;
@@ -1455,7 +1462,7 @@ hipError_t launch_segments_mp(const FastPlan& p, const LaunchArgs& a, const floa
 
 template <int R, int KS, int W, int MP, int WS>
 hipError_t launch_class(const FastClass& C, const FastArgs& f, int grid, int* queue, hipStream_t stream) {
-  auto kern = fast_batched_kernel<R, KS, W, MP, reg_waves(R, MP, W), WS>;
+  auto kern = fast_batched_kernel<R, KS, W, MP, reg_waves(R, KS, MP, W), WS>;
   const size_t lds = C.lds_bytes[W - 2][MP];
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);

@@ -1,0 +1,57 @@
+"""Register spills of the built gfx950 kernels, read from the metadata notes of libswarmsf.so's code objects (no GPU)."""
+import re
+import struct
+import subprocess
+
+import msgpack
+import pytest
+
+from paper_2501_19042_amd import _native
+
+
+def _kernels(path):
+    """{demangled name without arguments: metadata} of every kernel in the library's offload bundles."""
+    data = open(path, "rb").read()
+    found = {}
+    pos = data.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while pos >= 0:
+        (entries,) = struct.unpack_from("<Q", data, pos + 24)
+        p = pos + 32
+        for _ in range(entries):
+            off, size, idlen = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + idlen]:
+                found.update(_notes(data[pos + off:pos + off + size]))
+            p += 24 + idlen
+        pos = data.find(b"__CLANG_OFFLOAD_BUNDLE__", pos + 24)
+    names = subprocess.run(["c++filt"], input="\n".join(found), capture_output=True, text=True, check=True).stdout
+    short = (re.sub(r"^void |sf::|fastk::|\(anonymous namespace\)::", "", n).split("(")[0] for n in names.split("\n"))
+    return dict(zip(short, found.values()))
+
+
+def _notes(elf):
+    (phoff,) = struct.unpack_from("<Q", elf, 32)
+    (phnum,) = struct.unpack_from("<H", elf, 56)
+    for i in range(phnum):
+        kind, _, off, _, _, size = struct.unpack_from("<IIQQQQ", elf, phoff + 56 * i)
+        q = off
+        while kind == 4 and q < off + size:             # PT_NOTE
+            name, desc, note = struct.unpack_from("<III", elf, q)
+            d = q + 12 + ((name + 3) & ~3)
+            if note == 32:                              # NT_AMDGPU_METADATA
+                for k in msgpack.unpackb(elf[d:d + desc], raw=False)["amdhsa.kernels"]:
+                    yield k[".name"], k
+            q = d + ((desc + 3) & ~3)
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    _native.lib()                                       # raises if the library is not built
+    return _kernels(_native.LIB_PATH)
+
+
+def test_one_tile_instances_of_many_coefficients_do_not_spill(kernels):
+    """13 to 16 coefficients (KS = 4): the matrix rows of the multiplier/QP step do not fit beside the rest, and rows
+    spilled in the iteration cost up to half the speed.  At most the handful that KS = 3 spills around it."""
+    names = [n for n in kernels if re.match(r"fast_\w+_kernel<1, 4, ", n)]
+    assert len(names) >= 15
+    assert {n: kernels[n][".vgpr_spill_count"] for n in names if kernels[n][".vgpr_spill_count"] > 12} == {}
