@@ -55,3 +55,13 @@ def test_one_tile_instances_of_many_coefficients_do_not_spill(kernels):
     names = [n for n in kernels if re.match(r"fast_\w+_kernel<1, 4, ", n)]
     assert len(names) >= 15
     assert {n: kernels[n][".vgpr_spill_count"] for n in names if kernels[n][".vgpr_spill_count"] > 12} == {}
+
+
+@pytest.mark.parametrize("ks", [2, 3])
+@pytest.mark.parametrize("form", [1, 2])
+def test_workspace_instances_that_hold_their_operands(kernels, ks, form):
+    """Workspace instances at 168 registers (3 waves per SIMD) for batches that leave wave slots free, and for
+    persistent launches: nothing spills."""
+    for kernel in ("fast_project_kernel", "fast_batched_kernel"):
+        for waves in (2, 3):
+            assert kernels[f"{kernel}<1, {ks}, {waves}, {form}, 3, 1>"][".vgpr_spill_count"] == 0
