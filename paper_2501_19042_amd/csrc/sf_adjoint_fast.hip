@@ -862,8 +862,6 @@ size_t adj_lds(const DevCfg& c, int R, int KS, int W) { return (size_t)adj_fast_
 
 bool adjoint_fast_supported(const DevCfg& c) {
   if (c.D != 3 || c.n > 32 || c.m > 16 || c.H > 256) return false;
-  // (two robot tiles: the forward kernels that recompute the states start at nine coefficients)
-  if (c.n > 16 && c.m <= 8) return false;
   return adj_lds(c, 2, 4, 6) <= kAdjLds;
 }
 

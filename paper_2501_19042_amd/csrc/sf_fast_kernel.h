@@ -1486,9 +1486,8 @@ hipError_t launch_segments_instance(const FastPlan& p, const LaunchArgs& a, cons
 template <int MP, int WS, int R>
 hipError_t launch_segments_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
   constexpr int W = WS ? 3 : 4;
-  if constexpr (R == 1)
-    if (p.KS == 2) return launch_segments_instance<R, 2, W, MP, WS>(p, a, tab32, a16);
   switch (p.KS) {
+    case 2: return launch_segments_instance<R, 2, W, MP, WS>(p, a, tab32, a16);
     case 3: return launch_segments_instance<R, 3, W, MP, WS>(p, a, tab32, a16);
     case 4: return launch_segments_instance<R, 4, W, MP, WS>(p, a, tab32, a16);
     default: break;
@@ -1543,9 +1542,8 @@ hipError_t launch_single_w(const FastPlan& p, const LaunchArgs& a, const float* 
 }
 template <int MP, int WS, int R>
 hipError_t launch_single_mp(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16, int W) {
-  if constexpr (R == 1)
-    if (p.KS == 2) return launch_single_w<MP, WS, R, 2>(p, a, tab32, a16, W);
   switch (p.KS) {
+    case 2: return launch_single_w<MP, WS, R, 2>(p, a, tab32, a16, W);
     case 3: return launch_single_w<MP, WS, R, 3>(p, a, tab32, a16, W);
     case 4: return launch_single_w<MP, WS, R, 4>(p, a, tab32, a16, W);
     default: break;
