@@ -165,7 +165,10 @@ sf_status sf_project(sf_handle h, const sf_batch* batch, int32_t precision,
  * differentiated like the bound balls (their projection's 3x3 Jacobian).  The MFMA reverse sweep
  * serves batches whose every problem the MFMA kernels cover (up to 16 robots, no workspace); any
  * other batch runs the generic reverse sweep, which recomputes each checkpoint segment with the
- * generic FP32 (or FP64) iteration. */
+ * generic FP32 (or FP64) iteration.  The recomputed states live in a scratch buffer that the handle keeps
+ * until sf_destroy: several checkpoint segments up to 1/1024 of the device's memory, or one segment of any
+ * size.  Where the device has no room for several, fewer are taken at a time (SF_ENOMEM if not even one
+ * fits); a call that needs a larger buffer than the last allocates, so it cannot be captured. */
 sf_status sf_project_backward(sf_handle h, const sf_batch* batch, int32_t precision,
                               const void* xi_bar, const void* bvals, int32_t iters,
                               const void* ckpt, int32_t ckpt_every,

@@ -6,6 +6,7 @@
 #include "sf_f64.h"
 #include "sf_adjoint.h"
 #include "sf_eqqp.h"
+#include "sf_scratch.h"
 
 #include <algorithm>
 #include <cmath>
@@ -253,8 +254,8 @@ struct Plan {
 struct sf_handle_s {
   int device = 0;
   int ncu = 256;                 // compute units of that device
-  void* scratch = nullptr;       // adjoint recompute states, grown on demand
-  size_t scratch_bytes = 0;
+  size_t segment_states = 0;     // bytes of recomputed states per group of checkpoint segments
+  sf::Scratch scratch;           // adjoint recompute states, grown on demand
   void* eq_part = nullptr;       // per-chunk partial sums of the equality layer's reverse mode
   size_t eq_part_bytes = 0;
   std::vector<HostCfg> cfgs;
@@ -641,9 +642,19 @@ sf_status get_eq_chunks(sf_handle h, Plan* p) {
   return SF_OK;
 }
 
-// Bytes of recomputed states that one group of checkpoint segments may take in the scratch (one segment may
-// take more): ten segments of ten iterations of 16 robots x 512 samples are 238 MB.
-constexpr size_t kSegmentStates = (size_t)256 << 20;
+// Bytes of recomputed states that one group of checkpoint segments may take in the scratch (one segment may take
+// more): a thousandth of the device's memory (288 MB of 288 GB), since the handle keeps the buffer.  Several segments
+// in one launch pay where one leaves the chip waiting for set-ups (16 robots x 512 samples, ten segments of ten
+// iterations, 238 MB: 70 us each, 440 us together); larger segments have the samples or the iterations to cover that.
+constexpr size_t kSegmentShare = 1024;
+
+// hipMalloc that leaves no error behind for the next launch's check.
+void* device_alloc(size_t bytes) {
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
 
 // Reverse mode on the matrix cores (fp32; batches the MFMA forward kernels cover).  The checkpoint segments
 // are taken in groups, last first: the forward MFMA kernel recomputes the states of a group's segments from
@@ -657,19 +668,15 @@ sf_status adjoint_fast_path(sf_handle h, Plan* p, int32_t precision, const void*
   const int64_t stride = p->total_coef;
   const int nseg = (iters + ckpt_every - 1) / ckpt_every;
   const int64_t seg_states = (int64_t)2 * (std::min(ckpt_every, iters) + 1) * stride;   // elements per segment
-  const int64_t fit = std::max<int64_t>(1, (int64_t)(kSegmentStates / sizeof(float)) / seg_states);
-  const int group = p->fast.batched ? 1 : (int)std::min<int64_t>(std::min<int64_t>(nseg, fit), INT32_MAX / p->n_items);
+  const int64_t fit = std::max<int64_t>(1, (int64_t)(h->segment_states / sizeof(float)) / seg_states);
+  const int64_t most = p->fast.batched ? 1 : std::min<int64_t>(std::min<int64_t>(nseg, fit), INT32_MAX / p->n_items);
   const int every = std::min(ckpt_every, iters);   // slots per segment in the scratch
-  // states, carries and pend
-  const size_t need = ((size_t)group * seg_states + (size_t)4 * stride) * sizeof(float);
-  if (need > h->scratch_bytes) {
-    if (h->scratch) (void)hipFree(h->scratch);
-    h->scratch = nullptr;
-    h->scratch_bytes = 0;
-    if (hipMalloc(&h->scratch, need) != hipSuccess) return fail(SF_ENOMEM, "adjoint scratch allocation failed");
-    h->scratch_bytes = need;
-  }
-  float* carry = static_cast<float*>(h->scratch);
+  // carries and pend, and the states of as many segments as the device has room for
+  const int group = (int)sf::scratch_parts(h->scratch, (size_t)4 * stride * sizeof(float),
+                                           (size_t)seg_states * sizeof(float), most, device_alloc,
+                                           [](void* q) { (void)hipFree(q); });
+  if (group < 1) return fail(SF_ENOMEM, "adjoint scratch allocation failed");
+  float* carry = static_cast<float*>(h->scratch.ptr);
   float* pend = carry + 3 * stride;
   float* states = pend + stride;
   const hipStream_t s = static_cast<hipStream_t>(stream);
@@ -790,6 +797,8 @@ sf_status sf_setup(const sf_config* cfgs, int32_t n_cfgs, sf_handle* out) {
   }
   if (hipDeviceGetAttribute(&h->ncu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || h->ncu < 1)
     h->ncu = 256;
+  size_t memory = 0;
+  if (hipDeviceTotalMem(&memory, h->device) == hipSuccess) h->segment_states = memory / kSegmentShare;
   std::vector<double> all;
   std::vector<sf::DevCfg> devs;
   for (int i = 0; i < n_cfgs; ++i) {
@@ -885,7 +894,7 @@ void sf_destroy(sf_handle h) {
   for (Plan* p : h->plans) free_plan(p);
   if (h->d_tables) (void)hipFree(h->d_tables);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
-  if (h->scratch) (void)hipFree(h->scratch);
+  if (h->scratch.ptr) (void)hipFree(h->scratch.ptr);
   if (h->eq_part) (void)hipFree(h->eq_part);
   delete h;
 }
@@ -1071,14 +1080,8 @@ sf_status sf_project_backward(sf_handle h, const sf_batch* batch, int32_t precis
   sf::AdjointArgs a{};
   a.state_stride = (int64_t)2 * (ckpt_every + 1) * max_ndm;   // xi and lambda states of a segment
   const size_t need = (size_t)p->n_items * a.state_stride * elem;
-  if (need > h->scratch_bytes) {
-    if (h->scratch) (void)hipFree(h->scratch);
-    h->scratch = nullptr;
-    h->scratch_bytes = 0;
-    hipError_t e = hipMalloc(&h->scratch, need);
-    if (e != hipSuccess) return fail(SF_ENOMEM, "adjoint scratch allocation failed");
-    h->scratch_bytes = need;
-  }
+  if (sf::scratch_parts(h->scratch, 0, need, 1, device_alloc, [](void* q) { (void)hipFree(q); }) < 1)
+    return fail(SF_ENOMEM, "adjoint scratch allocation failed");
   a.cfgs = h->d_cfgs;
   a.probs = p->d_probs;
   a.items = p->d_items;
@@ -1087,7 +1090,7 @@ sf_status sf_project_backward(sf_handle h, const sf_batch* batch, int32_t precis
   a.ckpt_stride = p->total_coef;
   a.g_xi_out = g_xi_out; a.g_lam_out = g_lam_out; a.g_resid = g_resid; a.w_fpr = w_fpr;
   a.g_xi0 = g_xi0; a.g_lam0 = g_lam0; a.g_xi_bar = g_xi_bar;
-  a.states = h->scratch;
+  a.states = h->scratch.ptr;
   a.stream = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (precision == SF_FP64) {
