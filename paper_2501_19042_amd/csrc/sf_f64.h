@@ -13,7 +13,8 @@ bool f64_cfg_covered(const DevCfg& c);
 int64_t a64_entries(const DevCfg& c);
 void a64_fill(const DevCfg& c, const double* P3, double* out);
 // Waves per sample for a batch of these configs with R robot tiles of 16, and its LDS bytes; 0: it does
-// not fit.  The solve over the batch's work items; a.tab the FP64 factor table, D the configs' dimensions.
+// not fit, or its units are out of the range of fp32 drift bounds.  The solve over the batch's work items;
+// a.tab the FP64 factor table, D the configs' dimensions.
 int f64_waves(const DevCfg* const* cfgs, int n_cfgs, int R, int64_t n_items, int ncu, size_t* lds);
 hipError_t launch_f64_project(const LaunchArgs& a, const double* a64, int D, int R, int W);
 

@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cfloat>
+#include <cmath>
 
 namespace sf {
 namespace {
@@ -316,7 +317,7 @@ f64_project_kernel(F64Args A) {
               dw = fmaf(mx * mx, fwi[d], dw);
               er |= !(px[d] <= (d == 2 ? fskz : fskx));
             }
-            dn = __builtin_amdgcn_sqrtf(dn);
+            dn = __builtin_amdgcn_sqrtf(dn) + 2e-19f;   // (squares below the smallest float vanish)
             sv -= fLv * dn;
             sacc -= fLa * dn;
             if (ws_on) sws -= __builtin_amdgcn_sqrtf(dw);
@@ -1020,10 +1021,21 @@ bool f64_cfg_covered(const DevCfg& c) {
   return c.n <= 32 && c.m <= 16 && c.H <= 256 && f64_lds_bytes(c, c.n <= 16 ? 1 : 2, c.n <= 16 ? 4 : 3) <= kLds;
 }
 
+// Whether the drift bounds can be kept in fp32: their squares must neither vanish nor overflow, so every length and
+// rate of the config lies between 1e-9 and 1e9 of its units (in kilometres the workloads here have 1e-4, in
+// millimetres 1e4).  Swarms outside, in units of 1e-22 m for instance, go through the kernel without such bounds.
+static bool f64_units_covered(const DevCfg& c) {
+  auto in = [](double v) { return v >= 1e-9 && v <= 1e9; };
+  return in(c.a) && in(c.b) && (!c.vel_on || in(c.vmax)) && (!c.acc_on || in(c.amax)) &&
+         (!c.ws_on || (in(c.ws_a) && in(1.0 / sqrt(c.ws_ib2))));
+}
+
 // Waves per sample: with one robot tile 8 while every sample has a CU of its own (one time tile per wave
 // up to a horizon of 128), else 4, which keeps two samples per CU; with two robot tiles the LDS holds 4, or
 // 3 at the largest polynomials.
 int f64_waves(const DevCfg* const* cfgs, int n_cfgs, int R, int64_t n_items, int ncu, size_t* lds) {
+  for (int i = 0; i < n_cfgs; ++i)
+    if (!f64_units_covered(*cfgs[i])) return 0;
   for (int W : {8, 4, 3}) {
     if (W == 8 && (R == 2 || n_items > ncu)) continue;
     if (W == 3 && R == 1) continue;
