@@ -358,12 +358,12 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
             const float d1 = __uint_as_float(sdx[(par * 3 + 1) * NR + lane]);
             const float d2 = __uint_as_float(sdx[(par * 3 + 2) * NR + lane]);
             const float dn = __builtin_amdgcn_sqrtf(d0 * d0 + d1 * d1 + d2 * d2);
-            px += d0;
-            py += d1;
-            pz += d2;
-            sv -= Lv * dn;
-            sacc -= La * dn;
-            if (ws_on) sws -= __builtin_amdgcn_sqrtf((d0 * d0 + d1 * d1) * wia2 + d2 * d2 * wib2);
+            px = drift_add(px, d0);
+            py = drift_add(py, d1);
+            pz = drift_add(pz, d2);
+            sv = slack_less(sv, Lv * dn);
+            sacc = slack_less(sacc, La * dn);
+            if (ws_on) sws = slack_less(sws, __builtin_amdgcn_sqrtf((d0 * d0 + d1 * d1) * wia2 + d2 * d2 * wib2));
             er = !(px <= skx && py <= skx && pz <= skz);
             ev = !(sv > 1e-4f * vmax);
             ea = !(sacc > 1e-4f * amax);

@@ -312,15 +312,15 @@ f64_project_kernel(F64Args A) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
               const float mx = __uint_as_float(sdx[d * NR + lane]);
-              px[d] += mx;
+              px[d] = drift_add(px[d], mx);
               dn = fmaf(mx, mx, dn);
               dw = fmaf(mx * mx, fwi[d], dw);
               er |= !(px[d] <= (d == 2 ? fskz : fskx));
             }
             dn = __builtin_amdgcn_sqrtf(dn) + 2e-19f;   // (squares below the smallest float vanish)
-            sv -= fLv * dn;
-            sacc -= fLa * dn;
-            if (ws_on) sws -= __builtin_amdgcn_sqrtf(dw);
+            sv = slack_less(sv, fLv * dn);
+            sacc = slack_less(sacc, fLa * dn);
+            if (ws_on) sws = slack_less(sws, __builtin_amdgcn_sqrtf(dw));
             ev = !(sv > 1e-4f * fvmax);
             ea = !(sacc > 1e-4f * famax);
             ew = !(sws > 1e-4f);

@@ -140,4 +140,10 @@ hipError_t launch_feasibility(const DevCfg* cfgs, const double* tab64, const Dev
 size_t generic_lds_bytes(const DevCfg& c, int tile, size_t elem);
 size_t feasibility_lds_bytes(const DevCfg& c, int tile);
 
+// Drift bounds over many iterations in fp32: a sum of non-negative steps, and a slack less such steps.  A plain sum
+// loses up to half a unit in its last place with each step (all of it once the steps are that small), which over
+// thousands of iterations exceeds the margins of the tests; the term of 1.8e-7, three such halves, outweighs it.
+__host__ __device__ inline float drift_add(float sum, float step) { return fmaf(sum, 1.8e-7f, sum + step); }
+__host__ __device__ inline float slack_less(float slack, float step) { return slack - fmaf(fabsf(slack), 1.8e-7f, step); }
+
 }  // namespace sf
