@@ -21,8 +21,7 @@ ClassFn fast_class_p0_w0_r1, fast_class_p0_w0_r2, fast_class_p0_w1_r1, fast_clas
 ClassFn fast_class_p1_w0_r1, fast_class_p1_w0_r2, fast_class_p1_w1_r1, fast_class_p1_w1_r2;
 ClassFn fast_class_p2_w0_r1, fast_class_p2_w0_r2, fast_class_p2_w1_r1, fast_class_p2_w1_r2;
 SegmentsFn fast_segments_p0_w0_r1, fast_segments_p0_w0_r2, fast_segments_p0_w1_r1, fast_segments_p0_w1_r2;
-SegmentsFn fast_segments_p1_w0_r1, fast_segments_p1_w0_r2, fast_segments_p1_w1_r1, fast_segments_p1_w1_r2;
-SegmentsFn fast_segments_p2_w0_r1, fast_segments_p2_w0_r2, fast_segments_p2_w1_r1, fast_segments_p2_w1_r2;
+SegmentsFn fast_segments_p1_w0_r1, fast_segments_p2_w0_r1;
 // [fp32, bf16, fp16][workspace][robot tiles - 1]
 static SingleFn* const kSingle[3][2][2] = {
     {{fast_single_p0_w0_r1, fast_single_p0_w0_r2}, {fast_single_p0_w1_r1, fast_single_p0_w1_r2}},
@@ -32,10 +31,11 @@ static ClassFn* const kClass[3][2][2] = {
     {{fast_class_p0_w0_r1, fast_class_p0_w0_r2}, {fast_class_p0_w1_r1, fast_class_p0_w1_r2}},
     {{fast_class_p1_w0_r1, fast_class_p1_w0_r2}, {fast_class_p1_w1_r1, fast_class_p1_w1_r2}},
     {{fast_class_p2_w0_r1, fast_class_p2_w0_r2}, {fast_class_p2_w1_r1, fast_class_p2_w1_r2}}};
+// (a workspace and two robot tiles have their states recomputed in fp32 whatever the forward's form)
 static SegmentsFn* const kSegments[3][2][2] = {
     {{fast_segments_p0_w0_r1, fast_segments_p0_w0_r2}, {fast_segments_p0_w1_r1, fast_segments_p0_w1_r2}},
-    {{fast_segments_p1_w0_r1, fast_segments_p1_w0_r2}, {fast_segments_p1_w1_r1, fast_segments_p1_w1_r2}},
-    {{fast_segments_p2_w0_r1, fast_segments_p2_w0_r2}, {fast_segments_p2_w1_r1, fast_segments_p2_w1_r2}}};
+    {{fast_segments_p1_w0_r1, nullptr}, {nullptr, nullptr}},
+    {{fast_segments_p2_w0_r1, nullptr}, {nullptr, nullptr}}};
 
 // Resets the queue heads of a launch sequence (a kernel node rather than a memset, so the
 // sequence can be captured in a graph).
@@ -302,7 +302,12 @@ hipError_t fast_launch_segments(const FastPlan& p, const LaunchArgs& a, const fl
                                 int precision) {
   const int mp = instance_row(precision);
   if (mp < 0) return hipErrorNotSupported;
-  return kSegments[mp][p.ws][p.R - 1](p, a, tab32, static_cast<const uint4*>(a16));
+  SegmentsFn* const f = kSegments[mp][p.ws][p.R - 1];
+  if (!f) {
+    g_fast_err = "checkpoint segments of this shape are recomputed in fp32";
+    return hipErrorNotSupported;
+  }
+  return f(p, a, tab32, static_cast<const uint4*>(a16));
 }
 
 hipError_t fast_launch_single(const FastPlan& p, const LaunchArgs& a, const float* tab32, const void* a16,

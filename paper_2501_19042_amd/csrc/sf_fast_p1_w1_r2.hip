@@ -11,8 +11,4 @@ hipError_t fast_class_p1_w1_r2(const FastPlan& p, const LaunchArgs& a, const flo
   return fastk::launch_batched_mp<1, 1, 2>(p, a, tab32, a16, ci, grid, W);
 }
 
-hipError_t fast_segments_p1_w1_r2(const FastPlan& p, const LaunchArgs& a, const float* tab32, const uint4* a16) {
-  return fastk::launch_segments_mp<1, 1, 2>(p, a, tab32, a16);
-}
-
 }  // namespace sf

@@ -65,3 +65,14 @@ def test_workspace_instances_that_hold_their_operands(kernels, ks, form):
     for kernel in ("fast_project_kernel", "fast_batched_kernel"):
         for waves in (2, 3):
             assert kernels[f"{kernel}<1, {ks}, {waves}, {form}, 3, 1>"][".vgpr_spill_count"] == 0
+
+
+def test_segments_are_built_where_they_are_launched(kernels):
+    """Checkpoint segments of batches with a workspace or two robot tiles are recomputed in fp32 (operand form 0)."""
+    forms = set()
+    for n in kernels:
+        if n.startswith("fast_segments_kernel<"):
+            r, ks, _, form, _, ws = re.findall(r"\d+", n)
+            forms.add((r, ks, ws, form))
+    assert forms == {(r, ks, ws, form) for r in "12" for ks in "234" for ws in "01" for form in "012"
+                     if form == "0" or (r == "1" and ws == "0")}
