@@ -254,7 +254,7 @@ struct Plan {
 struct sf_handle_s {
   int device = 0;
   int ncu = 256;                 // compute units of that device
-  size_t segment_states = 0;     // bytes of recomputed states per group of checkpoint segments
+  size_t memory = 0;             // of that device (asked for by the first reverse mode)
   sf::Scratch scratch;           // adjoint recompute states, grown on demand
   void* eq_part = nullptr;       // per-chunk partial sums of the equality layer's reverse mode
   size_t eq_part_bytes = 0;
@@ -668,7 +668,8 @@ sf_status adjoint_fast_path(sf_handle h, Plan* p, int32_t precision, const void*
   const int64_t stride = p->total_coef;
   const int nseg = (iters + ckpt_every - 1) / ckpt_every;
   const int64_t seg_states = (int64_t)2 * (std::min(ckpt_every, iters) + 1) * stride;   // elements per segment
-  const int64_t fit = std::max<int64_t>(1, (int64_t)(h->segment_states / sizeof(float)) / seg_states);
+  if (h->memory == 0 && hipDeviceTotalMem(&h->memory, h->device) != hipSuccess) h->memory = 0;
+  const int64_t fit = std::max<int64_t>(1, (int64_t)(h->memory / kSegmentShare / sizeof(float)) / seg_states);
   const int64_t most = p->fast.batched ? 1 : std::min<int64_t>(std::min<int64_t>(nseg, fit), INT32_MAX / p->n_items);
   const int every = std::min(ckpt_every, iters);   // slots per segment in the scratch
   // carries and pend, and the states of as many segments as the device has room for
@@ -797,8 +798,6 @@ sf_status sf_setup(const sf_config* cfgs, int32_t n_cfgs, sf_handle* out) {
   }
   if (hipDeviceGetAttribute(&h->ncu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || h->ncu < 1)
     h->ncu = 256;
-  size_t memory = 0;
-  if (hipDeviceTotalMem(&memory, h->device) == hipSuccess) h->segment_states = memory / kSegmentShare;
   std::vector<double> all;
   std::vector<sf::DevCfg> devs;
   for (int i = 0; i < n_cfgs; ++i) {
