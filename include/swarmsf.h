@@ -148,8 +148,10 @@ void sf_destroy(sf_handle h);
  * Kernel choice is per problem: with SF_FP32, SF_BF16 or SF_FP16 the problems of a shape the MFMA
  * kernels cover (see SF_FP16) that fits their LDS plan run on them, and the other problems of the
  * batch on the generic kernel in FP32, in a second launch on the same stream (results of every
- * problem as in a batch of its own kind).  SF_FP64, SF_RESID_HISTORY and SF_GENERIC_KERNEL put the
- * whole batch on the generic kernel. */
+ * problem as in a batch of its own kind).  With SF_FP64 the FP64 matrix-core kernel takes the whole
+ * batch if every problem is of one dimension (2D or 3D), n_robots <= 32, degree <= 15, horizon <= 256,
+ * lengths and rates between 1e-9 and 1e9 of their units, and fits its LDS plan; else the generic kernel
+ * does.  SF_RESID_HISTORY and SF_GENERIC_KERNEL put the whole batch on the generic kernel. */
 sf_status sf_project(sf_handle h, const sf_batch* batch, int32_t precision,
                      const void* xi_bar, const void* bvals,
                      const void* xi0, const void* lam0, int32_t iters,
@@ -162,13 +164,15 @@ sf_status sf_project(sf_handle h, const sf_batch* batch, int32_t precision,
  * resid_out[:, 0] (g_resid, [S]) and of the fixed-point residual sum of SF_FP_RESIDUAL
  * (w_fpr, [S]) -- each may be NULL = zero -- it writes the gradients with respect to
  * xi0, lam0 and xi_bar (each may be NULL = not wanted).  The workspace rows of eq. (f_e) are
- * differentiated like the bound balls (their projection's 3x3 Jacobian).  The MFMA reverse sweep
- * serves batches whose every problem the MFMA kernels cover (up to 16 robots, no workspace); any
- * other batch runs the generic reverse sweep, which recomputes each checkpoint segment with the
- * generic FP32 (or FP64) iteration.  The recomputed states live in a scratch buffer that the handle keeps
- * until sf_destroy: several checkpoint segments up to 1/1024 of the device's memory, or one segment of any
- * size.  Where the device has no room for several, fewer are taken at a time (SF_ENOMEM if not even one
- * fits); a call that needs a larger buffer than the last allocates, so it cannot be captured. */
+ * differentiated like the bound balls (their projection's 3x3 Jacobian).  With SF_FP32, SF_BF16 or
+ * SF_FP16 the MFMA reverse sweep serves batches whose every problem the MFMA kernels cover (see
+ * sf_project); the states of a batch with more than 16 robots or a workspace are recomputed in fp32
+ * whatever the forward's form.  Any other batch runs the generic reverse sweep, which recomputes each
+ * checkpoint segment with the generic FP32 (or FP64) iteration.
+ *  The recomputed states live in a scratch buffer that the handle keeps until sf_destroy: several
+ *  checkpoint segments up to 1/1024 of the device's memory, or one segment of any size.  Where the
+ *  device has no room for several, fewer are taken at a time (SF_ENOMEM if not even one fits).  A call
+ *  that needs a larger buffer than the last allocates, so it cannot be captured. */
 sf_status sf_project_backward(sf_handle h, const sf_batch* batch, int32_t precision,
                               const void* xi_bar, const void* bvals, int32_t iters,
                               const void* ckpt, int32_t ckpt_every,
@@ -214,9 +218,9 @@ sf_status sf_qp_equality_backward(sf_handle h, const sf_batch* batch, int32_t pr
  * them and the per-chunk partial sums in a fixed 16 MiB device array of the library (one per GPU,
  * located at sf_setup, held until the process ends).  It calls no allocating routine.
  *  Limits: at most 64 problems per call, and tables plus partial sums within the 16 MiB (about
- *  (n_chunks x largest n D 6) elements, chunks of max(1, 32768 / (n D m)) samples per problem;
- *  roughly 900K samples of 16 robots in FP32); beyond them SF_EUNSUPPORTED, before anything is
- *  enqueued.
+ *  (n_chunks x largest n D 6) elements, chunks of max(1, 32768 / (n D m)) samples per problem, or
+ *  fewer where a batch has less than 512 such chunks, so that about 512 share it; roughly 900K
+ *  samples of 16 robots in FP32); beyond them SF_EUNSUPPORTED, before anything is enqueued.
  *  Every call on one GPU shares that array, which keeps the last call's contents: calls that overlap
  *  in time on one GPU (any handle, any stream) race.  Nothing in it needs clearing: each call writes
  *  every entry it reads. */

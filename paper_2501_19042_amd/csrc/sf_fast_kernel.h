@@ -292,10 +292,11 @@ constexpr int waves_per_simd(int R, int MP, int W) { return R == 1 ? 3 : (W >= 3
 // Register budget, as waves per SIMD.  A CU takes four samples of three waves each.  At 168 registers they fill all
 // twelve wave slots, and after a kernel with other workgroups the last sample often finds no slots of its shape, which
 // costs another round: 16 robots x 1024 samples, 319 iterations, after a feasibility check took 1.75 ms against
-// 1.22.  At 128 registers slots are left over: 1.24 ms in any order (fp32 needs no more by itself).  The 16-bit
-// instances of up to 12 coefficients fit that with 5-12 spills.  Those of 13 to 16 do not: they
-// spilled 66-95 registers, most of them inside the iteration (16 robots, degree 13, bf16, 100 iterations: 1024
-// samples 1.76 ms at 128 registers, 0.85 at 168).  The plans count waves_per_simd.
+// 1.22.  At 128 registers slots are left over: 1.24 ms in any order.  The 16-bit instances of up to 12 coefficients
+// fit that with 5-12 spills, of which the iteration reloads one or two (11 in a workspace at two waves).  Those of 13
+// to 16 do not: they spilled 66-95 registers, most of them inside the iteration (16 robots, degree 13, bf16, 100
+// iterations: 1024 samples 1.76 ms at 128 registers, 0.85 at 168).  In fp32 124-155 registers are used as they come.
+// The plans count waves_per_simd.
 constexpr int reg_waves(int R, int KS, int MP, int W) {
   return R == 1 && MP != 0 && KS <= 3 ? 4 : waves_per_simd(R, MP, W);
 }
@@ -610,8 +611,8 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         // pair closes by at most twice the drift of a position: until the drift since then reaches half the
         // margin, less the rounding, every residual of the tile is exactly zero and the tile is skipped.  Once
         // the early iterations have separated the robots, most tiles are: over 300 iterations a quarter of the tiles
-        // is evaluated with 16 robots (1024 samples, bf16: 1.38 -> 1.26 ms), under half with 32 (4096 samples: 18.4
-        // ms before and after, the step bounds it) and few with 8 robots x 4 samples (318 -> 272 us).
+        // is evaluated with 16 robots (1024 samples, bf16: 1.38 ms with every tile, 1.28 so), under half with 32 (4096
+        // samples: 18.3 and 16.2 ms) and few with 8 robots x 4 samples (100 iterations, fp32: 340 and 296 us).
         unsigned need;
         {
           const bool force = rebuild || eval_flags != 0 || (WS && ws_eval);
@@ -971,7 +972,7 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
         // arithmetic after them; y and its means then reach the lanes of a robot through LDS, in this axis'
         // partials of wave 0, which no other wave reads.  With two lanes per row, half the waves idle, the step was
         // a fifth of an iteration with one robot tile and a third with two (16 robots x 1024 samples, bf16, 300
-        // iterations: 1.37 -> 1.32 ms; 32 robots x 4096: 19.7 -> 18.3 ms).
+        // iterations: 1.37 ms then and 1.32 so, every tile evaluated in both).
         for (int ax = wave; ax < 3; ax += W) {
           float* gp0 = smem + L.tiles + ax * (R * KS * 64);
           const int q4 = lane >> 4, rb = lane & 15;
@@ -1153,8 +1154,9 @@ __device__ __forceinline__ void fast_item(const FastArgs& A, int it, float* smem
 
       // ---- primal residual of the last step (dense over pairs) ----
       // Bound by the latency of its chains: operand splits, products, pair rounds.  The operands of both iterates
-      // are formed once, each tile's basis operands load together and the pair rounds go two at a time (13 robots
-      // in a workspace, 333 samples, 60 iterations, fp16: 278 -> 270 us for the whole solve).
+      // are formed once where the registers hold them, each tile's basis operands load together and the pair rounds go
+      // two at a time (13 robots in a workspace, 333 samples, 60 iterations, fp16: 268 us for the whole solve, 3% more
+      // with the operands formed per product).
       float rmax = 0.0f;   // its largest block norm (thread 0)
       if (resid_out || status_out) {
         float ss = 0.0f, mx = 0.0f;
